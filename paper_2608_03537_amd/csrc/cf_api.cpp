@@ -130,12 +130,33 @@ int pick_tile(int64_t M, int64_t N, int64_t K, int in_f32, int loop, int epi, bo
   return best;
 }
 
+// The 256 x 256 tile where it beats `idx` (a 128-row tile).  Both are priced in
+// rounds of one workgroup per CU; a round costs its k steps plus its start and
+// store.  Measured with every CU busy (us): 128 x 256 tiles 0.9 a 64-deep step
+// and 4 a round, 128 x 192 0.77, 128 x 128 0.55; 256 x 256 tiles 1.4 and 12.
+// Products on either side of the line: 4096 x 4096 x 1024 34 us against 39,
+// 16384 x 768 x 3072 72 against 80, 8192 x 2048 x 2048 57 against 67; but 8192 x
+// 1024 x 1024 27 against 21 and 2048 x 4096 x 4096 77 against 63 (half the CUs idle).
+int pick_big(int idx, int64_t M, int64_t N, int64_t K, int in_f32, int loop, int64_t batch) {
+  if (in_f32 || loop < 1) return idx;
+  const int big = find_gemm_kernel(0, 256, 256, loop, 0);
+  if (big < 0 || K / 64 < gemm_kernel(big).stages - 1) return idx;
+  auto rounds = [&](int64_t tm, int64_t tn) {
+    const int64_t wgs = (M + tm - 1) / tm * ((N + tn - 1) / tn) * batch;
+    return (double)((wgs + kAssumedCUs - 1) / kAssumedCUs);
+  };
+  const double kt = (double)(K / 64);
+  const int tn = gemm_kernel(idx).tn;
+  const double step = tn == 256 ? 0.9 : tn == 192 ? 0.77 : 0.55;
+  return rounds(256, 256) * (1.4 * kt + 12.0) < rounds(128, tn) * (step * kt + 4.0) ? big : idx;
+}
+
 // Chooses kernel and row path for a GEMM (+ row subgraph).  `epi` selects the
 // epilogue: 0 = plain (alpha, bias, store), 1 = row subgraph.  `need_rows` is
 // true when the subgraph has a row reduction (then rows must be completed
 // across tiles); without one any tiling is valid.
 cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int path, int epi, bool need_rows,
-                    bool probe_device, Plan& pl, bool allow_cluster = true) {
+                    bool probe_device, Plan& pl, bool allow_cluster = true, int64_t batch = 1) {
   pl = Plan();
   if (!allow_cluster && need_rows) {
     if (path == PATH_CLUSTER)
@@ -149,6 +170,7 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
   if (!need_rows) {
     pl.kidx = pick_tile(M, N, K, in_f32, loop, epi, false, 0);
     if (pl.kidx < 0) pl.kidx = pick_tile(M, N, K, in_f32, 0, epi, false, 0);
+    if (pl.kidx >= 0 && epi == 0) pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, batch);
     pl.mode = ROWS_LOCAL;
   } else {
     if (path == PATH_AUTO) {
@@ -192,6 +214,7 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     } else if (path == PATH_SPLIT) {
       pl.kidx = pick_tile(M, N, K, in_f32, loop, 2, false, 0);
       if (pl.kidx < 0) pl.kidx = pick_tile(M, N, K, in_f32, 0, 2, false, 0);
+      if (pl.kidx >= 0) pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, 1);
       pl.mode = ROWS_SPLIT;
     } else {
       return fail(CF_ERR_UNSUPPORTED, "unknown path %d", path);
@@ -245,6 +268,25 @@ cf_status run_rows(const Plan& pl, GemmRowsParams p, void* ws, hipStream_t st) {
   bind_workspace(pl, ws, p);
   if (pl.mode == ROWS_SPLIT) {
     RowEpi full = p.epi;
+    RowKernelParams f{};
+    f.M = p.M;
+    f.N = p.N;
+    f.P = p.ws_x;
+    f.ldp = p.N;
+    f.p_f32 = 1;
+    f.epi = full;
+    if (gemm_kernel(pl.kidx).epi == 0) {
+      // The plain product in fp32; the row pass runs every stage (it reads the
+      // residual and takes the statistics of the rows it holds).
+      f.rows_per_batch = p.M;
+      p.epi = RowEpi{};
+      p.epi.alpha = 1.0f;
+      p.epi.Y = p.ws_x;
+      p.epi.ldy = p.N;
+      p.epi.y_f32 = 1;
+      cf_status s = hip_status(launch_gemm_rows(p, pl.kidx, st), "GEMM launch");
+      return s != CF_OK ? s : hip_status(launch_row_kernel(f, st), "row pass launch");
+    }
     // The GEMM runs stage 1 only and publishes x and partial statistics.
     p.epi.norm = NORM_NONE;
     p.epi.act = ACT_NONE;
@@ -253,17 +295,10 @@ cf_status run_rows(const Plan& pl, GemmRowsParams p, void* ws, hipStream_t st) {
     p.epi.quant = 0;
     cf_status s = hip_status(launch_gemm_rows(p, pl.kidx, st), "GEMM launch");
     if (s != CF_OK) return s;
-    RowKernelParams f{};
-    f.M = p.M;
-    f.N = p.N;
-    f.P = p.ws_x;
-    f.ldp = p.N;
-    f.p_f32 = 1;
     f.finish = 1;
     f.cn = pl.cn;
     f.tn = pl.tn;
     f.part = p.ws_part;
-    f.epi = full;
     f.epi.alpha = 1.0f;
     f.epi.bias = nullptr;
     f.epi.R = nullptr;
@@ -627,7 +662,8 @@ cf_status cf_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, cf_dtype in, c
     if (outputs_alias(C, {A, B, (const void*)bias})) return fail(CF_ERR_ALIAS, "C aliases an input");
     if (M == 0 || batch == 0) return CF_OK;
     Plan pl;
-    if ((s = plan_rows(M, N, K, in == CF_F32, b_layout == CF_LAYOUT_NK, PATH_AUTO, 0, false, false, pl)) != CF_OK)
+    if ((s = plan_rows(M, N, K, in == CF_F32, b_layout == CF_LAYOUT_NK, PATH_AUTO, 0, false, false, pl, true,
+                       batch)) != CF_OK)
       return s;
     GemmRowsParams p{};
     p.batch = (int)batch;

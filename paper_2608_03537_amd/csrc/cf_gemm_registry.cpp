@@ -13,7 +13,8 @@ static std::vector<GemmKernel>& table() {
   static std::vector<GemmKernel> t;
   static std::once_flag once;
   std::call_once(once, [] {
-    for (auto get : {gemm_kernels_v2, gemm_kernels_v1, gemm_kernels_wr, gemm_kernels_split, gemm_kernels_kn}) {
+    for (auto get : {gemm_kernels_v2, gemm_kernels_v1, gemm_kernels_wr, gemm_kernels_split, gemm_kernels_kn,
+                     gemm_kernels_big}) {
       int n = 0;
       const GemmKernel* k = get(&n);
       t.insert(t.end(), k, k + n);
@@ -54,7 +55,10 @@ int resident_wgs(int idx) {
 
 hipError_t launch_gemm_rows(const GemmRowsParams& p, int idx, hipStream_t st) {
   const GemmKernel& k = table()[idx];
-  dim3 grid((unsigned)(8 * p.slots * p.cn), (unsigned)p.batch), block((unsigned)k.threads);
+  // 256-row tiles have one workgroup per tile; the others a whole number of
+  // row-block slots on each XCD.
+  dim3 grid(k.tm == 256 ? (unsigned)(p.num_rb * p.cn) : (unsigned)(8 * p.slots * p.cn), (unsigned)p.batch);
+  dim3 block((unsigned)k.threads);
   void* args[] = {const_cast<GemmRowsParams*>(&p)};
   // Without row clusters every tile has a workgroup of its own (grouped
   // order); with them, workgroups loop only when the grid was capped below

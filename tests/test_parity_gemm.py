@@ -92,3 +92,48 @@ def test_rowop_softmax():
     ref = O.softmax_rows(0.25 * S.astype(np.float64))
     np.testing.assert_allclose(got.sum(axis=1), 1.0, atol=1e-5)
     assert np.max(np.abs(got - ref)) < 1e-6
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("batch,M,N,K,out", [
+    (1, 4096, 4096, 1024, "bf16"),    # whole tiles, an even number of k steps
+    (1, 8165, 2080, 1088, "f32"),     # ragged last row block and column tile, an odd number of steps
+    (3, 2049, 2048, 1152, "bf16"),    # one row in the last row block, batched
+])
+def test_gemm_large_tile(batch, M, N, K, out, layout):
+    """Products large enough for the 256 x 256 tile, every element against an fp32 product.  Both sides sum K
+    products of unit-variance terms in fp32 (error about 2^-24 sqrt(K) each, K <= 1152: 2e-6 of the rms; 1e-5
+    allowed); bf16 stores round by at most 2^-8 of the value."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    A = torch.randn((batch, M, K), generator=g, device="cuda").bfloat16()
+    B = (torch.randn((K, N) if layout == "kn" else (N, K), generator=g, device="cuda") / K ** 0.5).bfloat16()
+    bias = torch.randn((N,), generator=g, device="cuda")
+    C = cf.gemm(A, B, b_layout=cf.CF_LAYOUT_KN if layout == "kn" else cf.CF_LAYOUT_NK, bias=bias, alpha=0.5,
+                out_dtype=torch.float32 if out == "f32" else torch.bfloat16)
+    torch.cuda.synchronize()
+    Bf = B.float() if layout == "kn" else B.float().t().contiguous()
+    for b in range(batch):
+        ref = 0.5 * (A[b].float() @ Bf) + bias
+        err = (C[b].float() - ref).abs()
+        assert float((err - (2.0 ** -8 * ref.abs() if out == "bf16" else 0.0)).max()) < 1e-5
+
+
+def test_split_path_large_tile():
+    """LayerNorm, GELU, row amax and codes over a product that takes the 256 x 256 tile: the row pass adds bias and
+    residual and takes the statistics itself.  Sampled rows against fp64; the bounds are the chain's (bf16 Z)."""
+    M, N, K = 4099, 4096, 1024
+    g = torch.Generator(device="cuda").manual_seed(5)
+    X = torch.randn((M, K), generator=g, device="cuda").bfloat16()
+    W = (torch.randn((N, K), generator=g, device="cuda") / K ** 0.5).bfloat16()
+    R = torch.randn((M, N), generator=g, device="cuda").bfloat16()
+    b = torch.randn((N,), generator=g, device="cuda")
+    Z, s, Q = cf.ln_gelu_amax(X, W, b, R)
+    torch.cuda.synchronize()
+    rows = list(range(0, M, 127)) + [M - 1]
+    x = X[rows].double() @ W.double().t().contiguous() + b.double() + R[rows].double()
+    x = x - x.mean(1, keepdim=True)
+    x = x / torch.sqrt(x.square().mean(1, keepdim=True) + 1e-5)
+    z = 0.5 * x * (1.0 + torch.erf(x / 2 ** 0.5))
+    assert float((Z[rows].double() - z).abs().max()) < 2e-2
+    assert torch.allclose(s[rows].double(), z.abs().amax(1) / 448.0, rtol=1e-3)
+    assert bool((Q.view(torch.uint8) & 0x7F).amax(1).eq(0x7E).all())     # the row maximum is coded as +-448
