@@ -240,14 +240,18 @@ cf_status cf_gemm_subgraph_noalloc(const cf_subgraph_args* a, void* hip_stream);
  * dataflow of Sec. IV-A), and the last workgroup of a row block to finish
  * sums their partials at commit.  Otherwise one workgroup per row block runs
  * all chunks and keeps the sum in registers.
- * Workspace: 0 bytes for the FFN, attention, and the MLP unless it splits
- * the chunks; then cf_b2bgemm_workspace() bytes, 16-byte aligned:
+ * Workspace: 0 bytes for the FFN, for the MLP unless it splits the chunks, and
+ * for attention unless it splits the keys (few queries against many keys:
+ * several workgroups then take a part of the keys each and the last to finish
+ * merges); then cf_b2bgemm_workspace() bytes, 16-byte aligned:
  * CF_B2B_WS_HEADER_BYTES of arrival counters (one 32-bit word per batch
- * entry and 128-row block), then the fp32 partial products.  Zero-fill the
- * header once before the first MLP call; every call leaves it all zero
- * again and the partials never reach into it, so later calls of any shape
- * find it valid.  Do not share the workspace with calls of another kind,
- * and do not let calls that share it overlap in time.
+ * entry and 128-row block, for attention 32-query block), then the fp32
+ * partial products.  The split MLP needs it (CF_ERR_WORKSPACE); attention
+ * without it, or with a smaller one, keeps the keys in one workgroup.
+ * Zero-fill the header once before the first call; every call leaves it all
+ * zero again and the partials never reach into it, so later calls of any
+ * shape find it valid.  Do not share the workspace with calls of another
+ * kind, and do not let calls that share it overlap in time.
  * ------------------------------------------------------------------------ */
 typedef enum { CF_MID_GELU_BIAS = 0, CF_MID_SOFTMAX = 1, CF_MID_RELU_BIAS = 2 } cf_mid_op;
 typedef enum { CF_OUT_STORE = 0, CF_OUT_BIAS_RESIDUAL_LN = 1, CF_OUT_BIAS_RELU = 2 } cf_out_op;

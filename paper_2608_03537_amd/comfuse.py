@@ -218,7 +218,9 @@ def workspace(nbytes, device, stream=None, kind="rows"):
     key = (str(device), _stream(stream), kind)
     ws = _ws_cache.get(key)
     if ws is None or ws.numel() < nbytes:
-        ws = torch.zeros(max(nbytes, 1 << 20), dtype=torch.uint8, device=device)
+        # made on the stream that will use it, so the zero-fill runs before the call
+        with torch.cuda.stream(stream):
+            ws = torch.zeros(max(nbytes, 1 << 20), dtype=torch.uint8, device=device)
         _ws_cache[key] = ws
     return ws
 
@@ -460,6 +462,22 @@ def b2b_mlp(X, W1t, b1, W2t, b2=None, *, out_relu=False, out=None, ws=None, stre
     return O
 
 
+def _attention_workspace(a, device, stream):
+    """The workspace of a call with few queries (it lets several workgroups
+    share a query block's keys), or None: the call then runs without it.
+    Nothing is allocated while a graph is being captured: there the zero-fill
+    would belong to the graph, and a later eager call would find it undone."""
+    if a.batch * ((a.M + 31) // 32) >= 256:
+        return None
+    need = cf_b2bgemm_workspace(a)
+    if need == 0:
+        return None
+    if _capturing():
+        ws = _ws_cache.get((str(device), _stream(stream), "b2b"))
+        return ws if ws is not None and ws.numel() >= need else None
+    return workspace(need, device, stream, kind="b2b")
+
+
 def b2b_attention(Q, K, V, scale=None, out=None, stream=None):
     """O = softmax(scale * Q K^T) V for Q [B, H, Lq, d], K, V [B, H, Lk, d] (bf16, contiguous)."""
     torch = _torch()
@@ -477,5 +495,6 @@ def b2b_attention(Q, K, V, scale=None, out=None, stream=None):
                   W2=_ptr(V), ldw2=d, sw2=Lk * d, w2_layout=CF_LAYOUT_KN,
                   out=CF_OUT_STORE, b2=None, R=None, ldr=0, sr=0, gamma=None, beta=None, eps=0.0,
                   O=_ptr(O), ldo=d, so=Lq * d)
-    _check(cf_b2bgemm(a, None, 0, _stream(stream)))
+    ws = _attention_workspace(a, Q.device, stream)
+    _check(cf_b2bgemm(a, _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
     return O

@@ -771,9 +771,20 @@ static size_t mlp_workspace(const cf_b2b_args* a) {
 }
 static_assert(kMlpSplitMaxWorkgroups <= kMlpMaxRowBlocks, "split MLP counters");
 
+// Workspace of attention with split keys: the counter region, then for every
+// (batch entry, 32-query block) and part 32 rows of fp32 O and (max, sum).
+static size_t attention_workspace(const cf_b2b_args* a) {
+  if (!a || a->struct_size != sizeof(cf_b2b_args) || a->mid != CF_MID_SOFTMAX || a->M <= 0 || a->batch <= 0 ||
+      a->N1 <= 0 || a->K != a->N2 || !b2b_attention_supported((int)std::min<int64_t>(a->K, 1 << 30)))
+    return 0;
+  const AttentionForm f = attention_form(a->M, a->batch, a->N1, (int)a->K);
+  if (f.nz < 2) return 0;
+  return kMlpCounterBytes + (size_t)((a->M + 31) / 32 * a->batch * f.nz) * 32 * (size_t)(a->K + 2) * 4;
+}
+
 size_t cf_b2bgemm_workspace(const cf_b2b_args* a) {
   try {
-    return mlp_workspace(a);
+    return mlp_workspace(a) + attention_workspace(a);
   } catch (...) {
     return 0;
   }
@@ -884,6 +895,18 @@ cf_status cf_b2bgemm(const cf_b2b_args* a, void* workspace, size_t ws_bytes, voi
         p.ws_part = reinterpret_cast<float*>(b + kMlpCounterBytes);
       }
       return hip_status(launch_b2b_mlp(p, st), "B2B MLP launch");
+    }
+    if (!ffn) {
+      // Without a workspace that holds the parts, a query block's keys stay in
+      // one workgroup.
+      const size_t need = attention_workspace(a);
+      p.cn = 1;
+      if (need > 0 && workspace && ws_bytes >= need && aligned16(workspace)) {
+        char* b = reinterpret_cast<char*>(workspace);
+        p.cn = attention_form(a->M, a->batch, a->N1, (int)a->K).nz;
+        p.ws_count = reinterpret_cast<unsigned*>(b);
+        p.ws_part = reinterpret_cast<float*>(b + kMlpCounterBytes);
+      }
     }
     return hip_status(ffn ? launch_b2b_ffn(p, st) : launch_b2b_attention(p, st), "B2B launch");
   } catch (...) {

@@ -18,6 +18,8 @@
 //
 // Each wave owns 32 complete query rows, so the softmax statistics need only
 // the lane pair (l, l^32) — no cross-wave or cross-workgroup exchange.
+#include <algorithm>
+
 #include "cf_gemm_tile.h"
 #include "comfuse.h"
 
@@ -91,25 +93,42 @@ __device__ __forceinline__ float lane_pair_max(float v) { return fmaxf(v, __shfl
 // uses the same maximum throughout, so the result is unchanged.
 // K and V blocks arrive by wave-wide direct loads, both key-major; the
 // second product reads V^T fragments with transposing LDS reads.
+//
+// Key groups.  QG waves own 32 queries each; KS groups of QG waves share the
+// same queries and take the key blocks in turn (block j belongs to group
+// j % KS), each group with a ring of its own, and their (maximum, sum, O)
+// merge through LDS at the end.  With KS = 1 and QG = 4 a CU needs two
+// workgroups to give every SIMD two waves and to keep enough bytes in flight;
+// few queries (a decoding step, short batches) do not make that many, and
+// each workgroup's key loop is then a serial chain.  See attention_form.
+//
+// Split keys.  With few workgroups even so, gridDim.z of them share a query
+// block, each with a contiguous part of the key blocks; each publishes its partial
+// (m, l, O) in the workspace and the last to finish merges them in order.
 // ===========================================================================
-template <int D>
+template <int D, int QG_, int KS_, int BK_>
 struct AttnShape {
-  static constexpr int TM = 128, TN = 64, NT = 256;
+  static constexpr int QG = QG_, KS = KS_;
+  static constexpr int NW = QG * KS, NT = 64 * NW;
+  static constexpr int TM = 32 * QG, TN = BK_;
+  static constexpr int NH = TN / 32;              // 32-key halves of a block
   static constexpr int KB = TN * D * 2;           // K block bytes (TN rows of D*2 bytes)
   static constexpr int VB = TN * D * 2;           // V block bytes (TN rows of D*2 bytes)
   static constexpr int STAGE = KB + VB;
-  static constexpr int LDS_RING = 2 * STAGE;
-  static constexpr int LDS_STORE = TM * (D * 2 + 8);
-  static constexpr int LDS = LDS_RING > LDS_STORE ? LDS_RING : LDS_STORE;
+  static constexpr int LDS_RING = KS * 2 * STAGE;
+  static constexpr int OROW = D * 4 + 16;         // merge: one query's fp32 O
+  static constexpr int LDS_OUT = KS == 1 ? TM * (D * 2 + 8) : NW * 32 * (OROW + 8) + 16;
+  static constexpr int LDS = LDS_RING > LDS_OUT ? LDS_RING : LDS_OUT;
   static constexpr int DK = D / 16;               // MFMA k steps over d
   static constexpr int BD = D / 32;               // output blocks over d
   static constexpr int KROW = D * 2;              // bytes per K row
   static constexpr int KCH = KROW / 16;           // 16-byte chunks per K row
-  static constexpr int NSA = 2 * DK;              // MFMAs of one S^T block (two 32-key halves)
-  static constexpr int NSB = 4 * BD;              // MFMAs of one P V block
+  static constexpr int NSA = NH * DK;             // MFMAs of one S^T block
+  static constexpr int NSB = 2 * NH * BD;         // MFMAs of one P V block
   using Out = TileShape<bf16_t, 1, BD, 4, 1, 128, 0>;
-  static_assert(D % 32 == 0 && D <= 128, "head dim");
-  static_assert(16 % NSA == 0 || NSA % 16 == 0, "softmax chunks per slot");
+  static_assert(D % 32 == 0 && D <= 128 && TN % 32 == 0, "head dim, key block");
+  static_assert(KS > 1 || QG == 4, "the staged store of one key group covers 128 rows");
+  static_assert(LDS <= 160 * 1024 && 2 * STAGE <= 65536, "LDS budget, ds offset field");
 };
 
 // Softmax state of one block for one lane (query row lane % 32).
@@ -119,13 +138,14 @@ struct SoftmaxStep {
   u32x4_t P[2][2];   // bf16 P^T fragments: [32-key half][MFMA step]
 };
 
-template <int D>
-__global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
-  using A = AttnShape<D>;
+template <int D, int QG, int KS, int BK>
+__global__ __launch_bounds__(64 * QG * KS, 2) void b2b_attention_kernel(B2BParams p) {
+  using A = AttnShape<D, QG, KS, BK>;
   __shared__ __attribute__((aligned(16))) char smem[A::LDS];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
   const int lr = lane & 31, lg = lane >> 5;
+  const int wq = KS == 1 ? wave : wave % QG, grp = KS == 1 ? 0 : wave / QG;   // query rows, key group
   // XCD-aware order: workgroups go round-robin over the 8 XCDs by linear id,
   // so linear id L runs on XCD L % 8.  Give each XCD a contiguous range of
   // (head, query block) pairs: the query blocks of one head then share that
@@ -140,11 +160,14 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
   const bf16_t* Kp = p.W1 + (int64_t)bz * p.sw1;
   const bf16_t* Vp = p.W2 + (int64_t)bz * p.sw2;
   const float sl2 = p.mid_scale * 1.4426950408889634f;   // scale * log2(e), > 0
-  const int NB = (Lk + A::TN - 1) / A::TN;
+  const int NBall = (Lk + A::TN - 1) / A::TN;
+  // key blocks [jb, je) of this workgroup
+  const int jb = KS == 1 ? 0 : (int)((int64_t)NBall * blockIdx.z / gridDim.z);
+  const int NB = KS == 1 ? NBall : (int)((int64_t)NBall * (blockIdx.z + 1) / gridDim.z);
   constexpr float kLazy = 8.0f;                           // rescale threshold (log2 units)
 
   // Q fragments (B operand of S^T = K Q^T): row m, 8 d per lane per step.
-  const int m = m0 + wave * 32 + lr;
+  const int m = m0 + wq * 32 + lr;
   const int mc = min(m, p.M - 1);
   u32x4_t qf[A::DK];
 #pragma unroll
@@ -166,27 +189,32 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
   constexpr int LPR = A::KCH;                   // lanes per row in one wave-wide load
   constexpr int RPI = 64 / LPR;                 // rows per instruction
   // Wave-wide direct loads of key block j (K, or V when v_t is true) into a
-  // ring stage.  Load ins of a wave covers rows in * RPI .. + RPI - 1, in =
-  // wave + 4 ins; both swizzles depend on the row only through
-  // (row & 15) = (4 wave + lane / LPR) & 15 (d = 128) or the row pair
-  // ((row >> 1) & 7, d = 64), which does not change with ins, so the lane's
-  // byte offset inside its rows is fixed and the rest is wave-uniform.  Rows
-  // past Lk (the last block only) are clamped, and masked out of P.
-  const int row0 = wave * RPI + lane / LPR;     // this lane's row in load 0
-  const uint32_t kl_off = (uint32_t)((lane / LPR) * p.ldw1 * 2 + (((lane % LPR) ^ kswz(row0)) << 4));
-  const uint32_t vl_off = (uint32_t)((lane / LPR) * p.ldw2 * 2 + (((lane % LPR) ^ vswz(row0)) << 4));
-  constexpr int NINS = A::TN / RPI / 4;   // direct loads per wave for one K or V block
+  // ring stage of this wave's group.  Load ins of a wave covers rows in * RPI
+  // .. + RPI - 1, in = wq + QG ins.  The V swizzle depends on the row only
+  // through bits that lane / LPR sets, the K swizzle (row & 15 for d = 128,
+  // (row >> 1) & 7 for d = 64) also through in % 4 or in % 2, which takes NP
+  // values over a wave's loads: the lane's byte offset inside its rows is one
+  // of NP fixed ones and the rest is wave-uniform.  Rows past Lk (the last
+  // block only) are clamped, and masked out of P.
+  constexpr int NP = A::KCH == 16 ? (QG >= 4 ? 1 : 4 / QG) : (QG >= 2 ? 1 : 2);
+  uint32_t kl_off[NP];
+#pragma unroll
+  for (int i = 0; i < NP; ++i)
+    kl_off[i] = (uint32_t)((lane / LPR) * p.ldw1 * 2 + (((lane % LPR) ^ kswz((wq + QG * i) * RPI + lane / LPR)) << 4));
+  const uint32_t vl_off = (uint32_t)((lane / LPR) * p.ldw2 * 2 + (((lane % LPR) ^ vswz(lane / LPR)) << 4));
+  constexpr int NINS = A::TN / RPI / QG;   // direct loads per wave for one K or V block
+  char* const ring = smem + grp * 2 * A::STAGE;
   // Load ins of this wave for key block j (K, or V when v_t is true) into a
   // ring stage; `full` (block j lies inside Lk) selects the wave-uniform form.
   auto issue_one = [&](int j, auto stage_t, auto v_t, int ins, bool full) {
     constexpr bool VS = decltype(v_t)::value;
-    char* dst = smem + decltype(stage_t)::value * A::STAGE + (VS ? A::KB : 0);
+    char* dst = ring + decltype(stage_t)::value * A::STAGE + (VS ? A::KB : 0);
     const bf16_t* src = VS ? Vp : Kp;
     const int64_t ld = VS ? p.ldw2 : p.ldw1;
-    const int in = wave + 4 * ins;
+    const int in = wq + QG * ins;
     if (full) {
       const char* base = reinterpret_cast<const char*>(src + (int64_t)(j * A::TN + in * RPI) * ld);
-      dma16(base + (VS ? vl_off : kl_off), dst + in * 1024);
+      dma16(base + (VS ? vl_off : kl_off[ins % NP]), dst + in * 1024);
     } else {
       const int row = in * RPI + lane / LPR;
       const int c = (lane % LPR) ^ (VS ? vswz(row) : kswz(row));
@@ -220,7 +248,8 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
     const int r = lane & 15;
     const int dcol = (lane & 16) + 4 * (r & 3);
     const int krow = 4 * lg + (r >> 2);
-    const uint32_t s0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)smem);
+    const uint32_t s0 =
+        (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)smem) + grp * 2 * A::STAGE;
 #pragma unroll
     for (int ks = 0; ks < A::DK; ++ks) kbase[ks] = s0 + koff(lr, 2 * ks + lg);
 #pragma unroll
@@ -240,46 +269,41 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
   float lsum = 0.0f;
 
   // One MFMA of an S^T block: 32-key half b, d step ks.
-  auto mma_s = [&](f32x16_t (&S)[2], int b, int ks, u32x4_t kf) {
+  auto mma_s = [&](f32x16_t (&S)[A::NH], int b, int ks, u32x4_t kf) {
     const f32x16_t zero = {};
     S[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, kf),
                                                    __builtin_bit_cast(bf16x8_t, qf[ks]), ks == 0 ? zero : S[b],
                                                    0, 0, 0);
   };
-  // Softmax of block j in 16 chunks (S is this lane's 32 scores, raw).
-  auto sm_chunk = [&](f32x16_t (&S)[2], int c, SoftmaxStep& st, int j, auto mask_t) {
+  // Softmax of block j (S is this lane's 16 NH scores, raw).
+  auto softmax_all = [&](f32x16_t (&S)[A::NH], int j, SoftmaxStep& st, auto mask_t) {
     constexpr bool MASK = decltype(mask_t)::value;
-    if (c < 4) {   // block maximum of the raw scores (scale > 0)
-      float t = c == 0 ? -INFINITY : st.bmax;
+    float t = -INFINITY;   // block maximum of the raw scores (scale > 0)
 #pragma unroll
-      for (int q = 0; q < 8; ++q) t = fmaxf(t, S[c >> 1][(c & 1) * 8 + q]);
-      st.bmax = t;
-    } else if (c == 4) {
-      st.bmax = lane_pair_max(st.bmax) * sl2;
-    } else if (c == 5) {
-      const float mnew = fmaxf(m_used, st.bmax);
-      st.need = mnew > m_used + kLazy;
-      const float m_eff = st.need ? mnew : m_used;
-      st.corr = __builtin_amdgcn_exp2f(m_used - m_eff);   // exactly 1 when the maximum in use stays
-      m_used = m_eff;
-    } else if (c < 14) {   // P = exp2(s * scale * log2e - m), 4 values per chunk
-      const float nm = -m_used;
+    for (int e = 0; e < 16 * A::NH; ++e) t = fmaxf(t, S[e >> 4][e & 15]);
+    st.bmax = lane_pair_max(t) * sl2;
+    const float mnew = fmaxf(m_used, st.bmax);
+    st.need = mnew > m_used + kLazy;
+    const float m_eff = st.need ? mnew : m_used;
+    // exactly 1 when the maximum in use stays (also at -infinity, with key groups)
+    st.corr = KS > 1 && !st.need ? 1.0f : __builtin_amdgcn_exp2f(m_used - m_eff);
+    m_used = m_eff;
+    // P = exp2(s * scale * log2e - m).  A key group whose scores so far are
+    // all -infinity keeps the maximum -infinity; its P are 0.
+    const float nm = KS > 1 && m_used == -INFINITY ? 0.0f : -m_used;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int e = (c - 6) * 4 + q;
-        float pv = __builtin_amdgcn_exp2f(fmaf(S[e >> 4][e & 15], sl2, nm));
-        if constexpr (MASK) {
-          const int key = j * A::TN + (e >> 4) * 32 + acc_row(e & 15, lane);
-          pv = key < Lk ? pv : 0.0f;
-        }
-        S[e >> 4][e & 15] = pv;
+    for (int e = 0; e < 16 * A::NH; ++e) {
+      float pv = __builtin_amdgcn_exp2f(fmaf(S[e >> 4][e & 15], sl2, nm));
+      if constexpr (MASK) {
+        const int key = j * A::TN + (e >> 4) * 32 + acc_row(e & 15, lane);
+        pv = key < Lk ? pv : 0.0f;
       }
-    } else if (c == 14) {
-      st.P[0][0] = pack_step(S[0], 0);
-      st.P[0][1] = pack_step(S[0], 1);
-    } else {
-      st.P[1][0] = pack_step(S[1], 0);
-      st.P[1][1] = pack_step(S[1], 1);
+      S[e >> 4][e & 15] = pv;
+    }
+#pragma unroll
+    for (int h = 0; h < A::NH; ++h) {
+      st.P[h][0] = pack_step(S[h], 0);
+      st.P[h][1] = pack_step(S[h], 1);
     }
   };
   auto rescale = [&](const SoftmaxStep& st) {
@@ -328,7 +352,7 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
     // vector element written inside the call, the compiler passed the
     // fragment's first register for all four pairs.
 #pragma unroll
-    for (int q = 0; q < 4; ++q)
+    for (int q = 0; q < 2 * A::NH; ++q)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         const uint32_t x = st.P[q >> 1][q & 1][e];
@@ -336,16 +360,16 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
       }
   };
   // S^T of block j from its K rows in LDS: one 16-byte read per MFMA, KLA
-  // reads ahead; MFMA i takes half i % 2 and d step i / 2, so the two
-  // halves' accumulation chains alternate.  No other LDS operation is issued
+  // reads ahead; MFMA i takes half i % NH and d step i / NH, so the halves'
+  // accumulation chains alternate.  No other LDS operation is issued
   // in between, so read i is complete once at most the KLA - 1 later ones
   // are outstanding.
-  auto s_block = [&](f32x16_t (&S)[2], auto stage_t, auto&& after_mma) {
+  auto s_block = [&](f32x16_t (&S)[A::NH], auto stage_t, auto&& after_mma) {
     constexpr int KST = decltype(stage_t)::value * A::STAGE;
     constexpr int KLA = 4;
     auto kread = [&](auto i_t) {
       constexpr int i = decltype(i_t)::value;
-      constexpr int h = i % 2, ks = i / 2;
+      constexpr int h = i % A::NH, ks = i / A::NH;
       return ds_read_b128_at<KST + h * 32 * A::KROW>(kbase[ks]);
     };
     u32x4_t kf[KLA];
@@ -354,83 +378,241 @@ __global__ __launch_bounds__(256, 2) void b2b_attention_kernel(B2BParams p) {
       constexpr int i = decltype(i_t)::value;
       constexpr int rest = A::NSA - 1 - i;
       lgkm_wait<(rest < KLA - 1 ? rest : KLA - 1)>(kf[i % KLA]);
-      mma_s(S, i % 2, i / 2, kf[i % KLA]);
+      mma_s(S, i % A::NH, i / A::NH, kf[i % KLA]);
       if constexpr (i + KLA < A::NSA) kf[(i + KLA) % KLA] = kread(std::integral_constant<int, i + KLA>{});
       after_mma(i_t);
       __builtin_amdgcn_sched_barrier(0);
     });
   };
-  auto softmax_all = [&](f32x16_t (&Sc)[2], int j, SoftmaxStep& st, auto mask_t) {
-#pragma unroll
-    for (int c = 0; c < 16; ++c) sm_chunk(Sc, c, st, j, mask_t);
-  };
-
-  f32x16_t S[2];
+  f32x16_t S[A::NH];
   SoftmaxStep st;
-  // Prologue: K and V of block 0 on their way into LDS stage 0.
+  // Prologue: K and V of the group's first block on their way into LDS stage 0.
   using S0_ = std::integral_constant<int, 0>;
   using S1_ = std::integral_constant<int, 1>;
-  issue_kv(0, S0_{});
-  // Step j: K(j) and V(j) are in stage j & 1 once every wave has passed the
-  // barrier, and every wave is then done with block j-1, so stage (j+1) & 1
-  // takes K(j+1) and V(j+1) (direct loads).  Then S^T(j), softmax, rescale
-  // and the P V of block j.  Two workgroups share a CU, so while one wave of
-  // a SIMD runs the softmax the other (from the other workgroup) can issue
-  // MFMAs.  The loop runs two blocks per trip so that the stage, and with it
-  // every LDS offset, is a compile-time constant.
-  // The next block's loads go one after every second MFMA of S^T(j): a
-  // wave's load issue waits while the CU's load path takes earlier loads,
-  // and MFMAs already issued keep the matrix core busy meanwhile (eight
-  // loads in a row at the barrier cost a quarter of the step).
-  static_assert(2 * NINS <= A::NSA / 2, "loads per S^T block");
+  if (KS == 1 || jb + grp < NB) issue_kv(jb + grp, S0_{});
+  // Step j: K(j) and V(j) are in the step's stage once every wave has passed
+  // the barrier, and every wave is then done with the group's previous block,
+  // so the other stage takes the group's next block (direct loads).  Then
+  // S^T(j), softmax, rescale and the P V of block j.  With KS = 1 two
+  // workgroups share a CU, so while one wave of a SIMD runs the softmax the
+  // other (from the other workgroup) can issue MFMAs.  The loop runs two
+  // steps per trip so that the stage, and with it every LDS offset, is a
+  // compile-time constant.
+  // The next block's loads go between the MFMAs of S^T(j): a wave's load issue
+  // waits while the CU's load path takes earlier loads, and MFMAs already
+  // issued keep the matrix core busy meanwhile (eight loads in a row at the
+  // barrier cost a quarter of the step).
+  constexpr int SPC = A::NSA / (2 * NINS) > 0 ? A::NSA / (2 * NINS) : 1;   // MFMAs per load
+  constexpr int LPM = 2 * NINS > A::NSA ? 2 * NINS / A::NSA : 1;          // loads per MFMA
   auto step = [&](int j, auto stage_t, auto next_t) {
     wait_vmcnt<0>();
     lds_sync();
-    // Load q of the next block (K for q < NINS, then V) after MFMA 2 q + 1.
+    if (KS > 1 && j >= NB) return;   // this group has no block in the last step
+    // Loads q of the next block (K for q < NINS, then V), spread over the MFMAs.
     auto loads = [&](auto full_t) {
       using FT = decltype(full_t);
       return [&](auto i_t) {
         constexpr int i = decltype(i_t)::value;
-        if constexpr (i % 2 == 1 && i / 2 < 2 * NINS) {
-          constexpr bool VS = i / 2 >= NINS;
-          issue_one(j + 1, next_t, std::integral_constant<bool, VS>{}, VS ? i / 2 - NINS : i / 2, FT::value);
-        }
+        static_for<0, LPM>([&](auto l_t) {
+          constexpr int q = i / SPC * LPM + decltype(l_t)::value;
+          if constexpr (i % SPC == SPC - 1 && q < 2 * NINS) {
+            constexpr bool VS = q >= NINS;
+            issue_one(j + KS, next_t, std::integral_constant<bool, VS>{}, VS ? q - NINS : q, FT::value);
+          }
+        });
       };
     };
     // The three cases are separate code paths so that the common one (the
     // next block lies inside Lk) keeps its wave-uniform addressing.
-    if (j + 2 < NB || (j + 2 == NB && (j + 2) * A::TN <= Lk)) s_block(S, stage_t, loads(std::true_type{}));
-    else if (j + 1 < NB) s_block(S, stage_t, loads(std::false_type{}));
+    if (j + KS < NB && (j + KS + 1) * A::TN <= Lk) s_block(S, stage_t, loads(std::true_type{}));
+    else if (j + KS < NB) s_block(S, stage_t, loads(std::false_type{}));
     else s_block(S, stage_t, [](auto) {});
-    if (j + 1 < NB) softmax_all(S, j, st, std::false_type{});
+    if (KS == 1 ? j + 1 < NB : (j + 1) * A::TN <= Lk) softmax_all(S, j, st, std::false_type{});
     else softmax_all(S, j, st, std::true_type{});
     rescale(st);
     pv_block(stage_t, st);
   };
-  for (int j = 0; j < NB; j += 2) {
-    step(j, S0_{}, S1_{});
-    if (j + 1 < NB) step(j + 1, S1_{}, S0_{});
+  // Every group runs the same number of steps (the barriers are the workgroup's).
+  for (int j = jb; j < NB; j += 2 * KS) {
+    step(j + grp, S0_{}, S1_{});
+    if (j + KS < NB) step(j + KS + grp, S1_{}, S0_{});
   }
 
   __syncthreads();
-  const float inv = 1.0f / lane_pair_sum(lsum);
+  if constexpr (KS == 1) {
+    const float inv = 1.0f / lane_pair_sum(lsum);
 #pragma unroll
-  for (int b = 0; b < A::BD; ++b)
+    for (int b = 0; b < A::BD; ++b)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) Oa[b][i] *= inv;
-  store_tile_staged<typename A::Out>(reinterpret_cast<f32x16_t(&)[1][A::BD]>(Oa), p.O + (int64_t)bz * p.so, p.ldo, 0, p.M, D, m0, 0, smem, tid, lane,
-                                     wave, 0);
+      for (int i = 0; i < 16; ++i) Oa[b][i] *= inv;
+    store_tile_staged<typename A::Out>(reinterpret_cast<f32x16_t(&)[1][A::BD]>(Oa), p.O + (int64_t)bz * p.so, p.ldo, 0, p.M, D, m0, 0, smem, tid, lane,
+                                       wave, 0);
+  } else {
+    // Every wave leaves its O (fp32, one padded row per query) and (m, l) in
+    // LDS; then thread t takes 8 consecutive d of one query and adds the
+    // groups in order, each scaled to the common maximum.
+    const float l = lane_pair_sum(lsum);
+    char* const orow = smem + (wave * 32 + lr) * A::OROW;
+#pragma unroll
+    for (int b = 0; b < A::BD; ++b)
+#pragma unroll
+      for (int g4 = 0; g4 < 4; ++g4)
+        *reinterpret_cast<f32x4_t*>(orow + (32 * b + 8 * g4 + 4 * lg) * 4) =
+            f32x4_t{Oa[b][4 * g4], Oa[b][4 * g4 + 1], Oa[b][4 * g4 + 2], Oa[b][4 * g4 + 3]};
+    float* const ml = reinterpret_cast<float*>(smem + A::NW * 32 * A::OROW);   // [wave][query][2]
+    int* const flag = reinterpret_cast<int*>(smem + A::NW * 32 * (A::OROW + 8));
+    if (lg == 0) {
+      ml[(wave * 32 + lr) * 2] = m_used;
+      ml[(wave * 32 + lr) * 2 + 1] = l;
+    }
+    __syncthreads();
+    constexpr int TPR = D / 8;                      // threads per query
+    constexpr int QPI = A::NT / TPR;                // queries per iteration
+    const int nz = gridDim.z, rows = min(A::TM, p.M - m0);
+    const int d0 = tid % TPR * 8;
+    uint16_t* const O = p.O + (int64_t)bz * p.so;
+    auto store8 = [&](int r, const float (&o)[8], float s) {
+      const u32x4_t w = {pack_bf16x2(o[0] * s, o[1] * s), pack_bf16x2(o[2] * s, o[3] * s),
+                         pack_bf16x2(o[4] * s, o[5] * s), pack_bf16x2(o[6] * s, o[7] * s)};
+      __builtin_nontemporal_store(w, reinterpret_cast<u32x4_t*>(O + (int64_t)(m0 + r) * p.ldo + d0));
+    };
+    // Partials of the query block (split keys): [z][row][D] O, then [z][row][2]
+    // (m, l), in the block's own region; device-coherent accesses, since the
+    // workgroups of a block need not share an XCD.
+    constexpr int kSc1 = 16;
+    float* const part = p.ws_part + (int64_t)g * nz * A::TM * (D + 2);
+    const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(part, 0, nz * A::TM * (D + 2) * 4, 0x00020000);
+    const int ml_off = nz * A::TM * D * 4;
+    for (int r = tid / TPR; r < rows; r += QPI) {
+      float mg[KS], M = -INFINITY, L = 0.0f, o[8] = {};
+#pragma unroll
+      for (int q = 0; q < KS; ++q) M = fmaxf(M, mg[q] = ml[((q * QG + r / 32) * 32 + r % 32) * 2]);
+#pragma unroll
+      for (int q = 0; q < KS; ++q) {
+        const int w = (q * QG + r / 32) * 32 + r % 32;
+        const float f = mg[q] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mg[q] - M);
+        L = fmaf(f, ml[w * 2 + 1], L);
+        const float* src = reinterpret_cast<const float*>(smem + w * A::OROW) + d0;
+        const f32x4_t a = *reinterpret_cast<const f32x4_t*>(src), b = *reinterpret_cast<const f32x4_t*>(src + 4);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          o[e] = fmaf(f, a[e], o[e]);
+          o[4 + e] = fmaf(f, b[e], o[4 + e]);
+        }
+      }
+      if (nz == 1) {
+        store8(r, o, 1.0f / L);
+      } else {
+        const int at = (blockIdx.z * A::TM + r) * D * 4 + d0 * 4;
+        const f32x4_t a = {o[0], o[1], o[2], o[3]}, b = {o[4], o[5], o[6], o[7]};
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, a), rsrc, at, 0, kSc1);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, b), rsrc, at + 16, 0, kSc1);
+        if (d0 == 0) {
+          const u32x2_t v = {__float_as_uint(M), __float_as_uint(L)};
+          __builtin_amdgcn_raw_buffer_store_b64(v, rsrc, ml_off + (blockIdx.z * A::TM + r) * 8, 0, kSc1);
+        }
+      }
+    }
+    if (nz == 1) return;
+    // Count the arrival; the last workgroup of the block merges (a counter goes
+    // back to 0, ready for the next call).
+    wait_vmcnt<0>();          // this wave's partial stores have completed
+    __syncthreads();          // ... and every wave's
+    if (tid == 0) {
+      const unsigned old = __hip_atomic_fetch_add(p.ws_count + g, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = old == (unsigned)(nz - 1);
+      if (last) __hip_atomic_store(p.ws_count + g, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *flag = last;
+    }
+    __syncthreads();
+    if (!*flag) return;
+    for (int r = tid / TPR; r < rows; r += QPI) {
+      float M = -INFINITY, L = 0.0f, o[8] = {};
+      // parts in order, rescaled to the running maximum, four loaded at a time
+      for (int z0 = 0; z0 < nz; z0 += 4) {
+        u32x4_t a[4], b[4];
+        u32x2_t v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int z = min(z0 + q, nz - 1), at = (z * A::TM + r) * D * 4 + d0 * 4;
+          a[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, kSc1);
+          b[q] = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at + 16, 0, kSc1);
+          v[q] = __builtin_amdgcn_raw_buffer_load_b64(rsrc, ml_off + (z * A::TM + r) * 8, 0, kSc1);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          if (z0 + q >= nz) break;
+          const float mz = __uint_as_float(v[q][0]), mn = fmaxf(M, mz);
+          const float fo = M == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(M - mn);
+          const float fz = mz == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(mz - mn);
+          M = mn;
+          L = fmaf(fz, __uint_as_float(v[q][1]), fo * L);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            o[e] = fmaf(fz, __uint_as_float(a[q][e]), fo * o[e]);
+            o[4 + e] = fmaf(fz, __uint_as_float(b[q][e]), fo * o[4 + e]);
+          }
+        }
+      }
+      store8(r, o, 1.0f / L);
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
 bool b2b_attention_supported(int d) { return d == 64 || d == 128; }
 
-hipError_t launch_b2b_attention(const B2BParams& p, hipStream_t st) {
-  const dim3 grid((unsigned)((p.M + 127) / 128), (unsigned)p.batch), block(256);
-  if (p.K == 128) hipLaunchKernelGGL((b2b_attention_kernel<128>), grid, block, 0, st, p);
-  else if (p.K == 64) hipLaunchKernelGGL((b2b_attention_kernel<64>), grid, block, 0, st, p);
-  else return hipErrorInvalidValue;
+template <int D, int QG, int KS, int BK>
+static hipError_t launch_attention(const B2BParams& p, int nz, hipStream_t st) {
+  using A = AttnShape<D, QG, KS, BK>;
+  const dim3 grid((unsigned)((p.M + A::TM - 1) / A::TM), (unsigned)p.batch, (unsigned)nz), block(A::NT);
+  hipLaunchKernelGGL((b2b_attention_kernel<D, QG, KS, BK>), grid, block, 0, st, p);
   return hipGetLastError();
+}
+
+// The workgroup form (query waves QG, 0 for two workgroups per CU with QG = 4
+// and one key group) and the number nz of workgroups that split a query
+// block's keys.  One workgroup of a several-group form fills a CU (128 KB of
+// rings, two waves per SIMD), so the form with the fewest queries per
+// workgroup that fits one generation of 256 CUs is taken, and the two-per-CU
+// form beyond.  Measured (us, heads x queries x keys x d; QG 1 / 2 / 4 / two
+// per CU): 8 x 345 x 345 x 64 5.7 / 6.5 / 7.8 / 8.3; 16 x 1000 x 1000 x 128
+// 24.4 / 16.4 / 19.6 / 22.5; 24 x 1000 x 1000 x 64 22.7 / 18.5 / 14.7 / 17.5;
+// 32 x 2048 x 2048 x 128 152 / 95 / 73 / 71.  Queries that fit one or two waves
+// take that form however many heads there are (256 x 1 x 4095 x 128 91 us, two
+// per CU 99).  Keys are split while workgroups are fewer than CUs and every
+// wave keeps two key blocks, at most eight ways (the last workgroup's merge
+// grows with them): 16 x 1 x 4095 x 128 34.5 us unsplit, 14.5 / 13.6 / 16.6 in
+// 4 / 8 / 16; 128 x 1 x 4095 x 128 65 and 50 in 2.
+AttentionForm attention_form(int64_t M, int64_t batch, int64_t Lk, int d) {
+  constexpr int64_t kCUs = 256;
+  auto wgs = [&](int qg) { return (M + 32 * qg - 1) / (32 * qg) * batch; };
+  AttentionForm f{0, 1};
+  if (M <= 32 || wgs(1) <= kCUs) f.qg = 1;
+  else if (M <= 64 || wgs(2) <= kCUs) f.qg = 2;
+  else if (wgs(4) <= kCUs) f.qg = 4;
+  if (f.qg == 1) {
+    const int64_t per_wave = (Lk + 31) / 32 / (d == 128 ? 4 : 8);   // key blocks of one wave, unsplit
+    f.nz = (int)std::max<int64_t>(1, std::min<int64_t>({kCUs / wgs(1), per_wave / 2, 8}));
+  }
+  return f;
+}
+
+hipError_t launch_b2b_attention(const B2BParams& p, hipStream_t st) {
+  const int qg = attention_form(p.M, p.batch, p.N1, p.K).qg;
+  if (p.K == 128) {
+    if (qg == 1) return launch_attention<128, 1, 4, 32>(p, p.cn, st);
+    if (qg == 2) return launch_attention<128, 2, 4, 32>(p, 1, st);
+    if (qg == 4) return launch_attention<128, 4, 2, 64>(p, 1, st);
+    return launch_attention<128, 4, 1, 64>(p, 1, st);
+  }
+  if (p.K == 64) {
+    if (qg == 1) return launch_attention<64, 1, 8, 32>(p, p.cn, st);
+    if (qg == 2) return launch_attention<64, 2, 4, 64>(p, 1, st);
+    if (qg == 4) return launch_attention<64, 4, 2, 64>(p, 1, st);
+    return launch_attention<64, 4, 1, 64>(p, 1, st);
+  }
+  return hipErrorInvalidValue;
 }
 
 }  // namespace cf

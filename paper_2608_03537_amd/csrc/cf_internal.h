@@ -146,9 +146,11 @@ struct B2BParams {
   // MLP (S = ReLU(P + b1)): output ReLU, and the split of N1 over cn
   // workgroups whose partial second products are summed at commit
   int out_relu;
-  int cn;                                  // workgroups per row block: N1 / 256 (split), or 1 (whole)
+  int cn;                                  // workgroups per row block: N1 / 256 (split), or 1 (whole);
+                                           // attention: workgroups that share a query block's keys
   unsigned* ws_count;                      // [batch][row blocks] arrival counters (zero between calls)
-  float* ws_part;                          // [batch][cn][M][N2] fp32 partial products
+  float* ws_part;                          // MLP: [batch][cn][M][N2] fp32 partial products; attention: per
+                                           // query block [cn][32][d] fp32 O, then [cn][32] (max, sum)
 };
 
 // Launchers (return hipSuccess or the launch error).
@@ -159,6 +161,8 @@ hipError_t launch_b2b_attention(const B2BParams& p, hipStream_t st);  // -> hipE
 hipError_t launch_b2b_mlp(const B2BParams& p, hipStream_t st);        // -> hipErrorInvalidValue if N2 not compiled
 bool b2b_ffn_supported(int N1, int N2);
 bool b2b_mlp_supported(int K, int N1, int N2);
+struct AttentionForm { int qg, nz; };   // 32-query waves per workgroup (0: two workgroups per CU), key parts
+AttentionForm attention_form(int64_t M, int64_t batch, int64_t Lk, int d);
 constexpr int kMlpRows = 128, kMlpHidden = 256;   // rows and hidden units of one MLP workgroup
 bool b2b_attention_supported(int d);
 

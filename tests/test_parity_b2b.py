@@ -159,3 +159,57 @@ def test_attention_full_size_sampled_rows():
             g = got[b, h][rows]
             assert rel_rms(g, ref) < 5e-3, (b, h, rel_rms(g, ref))
             assert max_abs(g, ref) < 2e-2, (b, h, max_abs(g, ref))
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("B,H,Lq,Lk", [
+    (1, 3, 1, 1),        # one query, one key: three of four key groups empty
+    (2, 16, 5, 33),      # two key blocks, the last of one key
+    (1, 2, 31, 1000),    # few queries, keys split over workgroups, ragged last block
+    (2, 8, 16, 4097),    # the same, one key past a block
+    (1, 9, 33, 290),     # two 32-query blocks
+    (70, 4, 33, 129),    # 32 < Lq <= 64: two query waves, four key groups
+    (5, 13, 250, 200),   # 195 64-query blocks
+    (4, 16, 511, 321),   # 256 128-query blocks: two key groups, an odd number of key blocks
+])
+def test_attention_key_groups(B, H, Lq, Lk, d):
+    """Shapes that take a form with several key groups per workgroup (and, with few queries, several workgroups per
+    query block), with the workspace and without it, against the oracle on some heads."""
+    g = torch.Generator(device="cuda").manual_seed(Lq + Lk)
+    Q, K, V = (torch.randn((B, H, n, d), generator=g, device="cuda").bfloat16() for n in (Lq, Lk, Lk))
+    got = [cf.b2b_attention(Q, K, V), cf.b2b_attention(Q, K, V)]
+    a = cf._b2b_args(batch=B * H, M=Lq, K=d, N1=Lk, N2=d, dtype=cf.CF_BF16, X=Q.data_ptr(), ldx=d, sx=Lq * d,
+                     W1=K.data_ptr(), ldw1=d, sw1=Lk * d, w1_layout=cf.CF_LAYOUT_NK, mid=cf.CF_MID_SOFTMAX,
+                     mid_scale=d ** -0.5, W2=V.data_ptr(), ldw2=d, sw2=Lk * d, w2_layout=cf.CF_LAYOUT_KN,
+                     out=cf.CF_OUT_STORE, ldo=d, so=Lq * d)
+    alone = torch.empty_like(Q)
+    a.O = alone.data_ptr()
+    cf._check(cf.cf_b2bgemm(a, None, 0, torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    assert torch.equal(got[0], got[1])
+    heads = [(0, 0), (B - 1, H - 1), (B // 2, H // 3)]
+    for b, h in heads:
+        q, k, v = (t[b:b + 1, h:h + 1].float().cpu().numpy() for t in (Q, K, V))
+        ref = O.attention(q, k, v)[0, 0]
+        for o in (got[0], alone):
+            o = o[b, h].float().cpu().numpy().astype(np.float64)
+            assert rel_rms(o, ref) < 5e-3 and max_abs(o, ref) < 2e-2
+    ws = cf._ws_cache.get((str(Q.device), torch.cuda.current_stream().cuda_stream, "b2b"))
+    if ws is not None:   # arrival counters are back at zero
+        assert int(ws[:cf.CF_B2B_WS_HEADER_BYTES].view(torch.int32).abs().sum()) == 0
+
+
+def test_attention_minus_infinity_scores_in_whole_key_groups():
+    """Keys whose scores are -infinity have weight 0, also where they are all of a key group's or of a part's: for
+    the even queries the products with every key from 20 on overflow to -infinity, the odd ones see all keys."""
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Q, K, V = (torch.randn((1, 2, n, 128), generator=g, device="cuda").bfloat16() for n in (7, 1500, 1500))
+    Q[:, :, ::2, 0], Q[:, :, 1::2, 0] = 4.0, 0.0
+    K[:, :, :20, 0], K[:, :, 20:, 0] = 0.0, -3e38
+    got = cf.b2b_attention(Q, K, V)
+    torch.cuda.synchronize()
+    for h in range(2):
+        sc = Q[0, h].double() @ K[0, h].double().t().contiguous() * 128 ** -0.5
+        sc[::2, 20:] = float("-inf")
+        ref = torch.softmax(sc, 1) @ V[0, h].double()
+        assert float((got[0, h].double() - ref).abs().max()) < 2e-2
