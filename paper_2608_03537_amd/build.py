@@ -22,7 +22,7 @@ ARCH = os.environ.get("CF_OFFLOAD_ARCH", "gfx950")
 SOURCES = ["cf_api.cpp", "cf_gemm_registry.cpp", "cf_gemm_inst_v2.hip", "cf_gemm_inst_v1.hip",
            "cf_gemm_inst_wr.hip", "cf_gemm_inst_split.hip", "cf_rows.hip", "cf_b2b.hip", "cf_ffn.hip",
            "cf_noalloc.hip", "cf_mlp.hip", "cf_gemm_inst_kn.hip",
-           "cf_gemm_big.hip"]
+           "cf_gemm_big.hip", "cf_gemm_small.hip"]
 
 # -packed-fp32-ops off: hipcc then never forms v_pk_{add,mul,fma}_f32 from
 # scalar float code (the host pass warns that it does not know the feature).
@@ -43,7 +43,7 @@ def _hipcc():
 # AGPRs would cost a copy each way for every such step.
 FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"]
               for f in ("cf_gemm_inst_v2.hip", "cf_gemm_inst_v1.hip", "cf_gemm_inst_wr.hip", "cf_gemm_inst_split.hip",
-                        "cf_gemm_inst_kn.hip", "cf_gemm_big.hip",
+                        "cf_gemm_inst_kn.hip", "cf_gemm_big.hip", "cf_gemm_small.hip",
                         "cf_b2b.hip", "cf_mlp.hip")}
 # The GEMM kernels' one atomic (a row-cluster round counter, added by lane 0
 # at the start of a tile) returns a value needed only after the main loop.
@@ -51,7 +51,7 @@ FILE_FLAGS = {f: ["-mllvm", "-amdgpu-mfma-vgpr-form"]
 # the result at once, which puts a wait for the atomic's round trip in front
 # of the first operand loads.
 for _f in ("cf_gemm_inst_v2.hip", "cf_gemm_inst_v1.hip", "cf_gemm_inst_wr.hip", "cf_gemm_inst_split.hip",
-           "cf_gemm_inst_kn.hip"):
+           "cf_gemm_inst_kn.hip", "cf_gemm_small.hip"):
     FILE_FLAGS[_f] = FILE_FLAGS[_f] + ["-mllvm", "-amdgpu-atomic-optimizer-strategy=None"]
 
 

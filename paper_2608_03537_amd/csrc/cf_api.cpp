@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <string>
+#include <utility>
 
 #include "comfuse.h"
 #include "cf_internal.h"
@@ -82,6 +83,7 @@ enum Path { PATH_AUTO = 0, PATH_WHOLE_ROW = 1, PATH_CLUSTER = 2, PATH_SPLIT = 3 
 constexpr int kWholeRowMaxN = 768;
 constexpr int kClusterMaxPeers = 16;
 constexpr int kAutoClusterPeers = 8;
+constexpr int kSmallMaxPeers = 32;   // small tiles: one per CU of an XCD
 
 struct Plan {
   int kidx = -1, mode = ROWS_LOCAL, cn = 1, num_rb = 0, slots = 0, tm = 0, tn = 0;
@@ -103,7 +105,8 @@ void size_workspace(Plan& pl, int64_t M, int64_t N, bool header) {
     pl.ws = kWsHeaderBytes;
   } else if (pl.mode == ROWS_SPLIT) {
     pl.off_part = header ? kWsHeaderBytes : 0;
-    pl.off_x = pl.off_part + round_up((size_t)M * pl.cn * 8, 256);
+    // a plain product (256 x 256 and small tiles) leaves no partial statistics
+    pl.off_x = pl.off_part + (gemm_kernel(pl.kidx).epi == 2 ? round_up((size_t)M * pl.cn * 8, 256) : 0);
     pl.ws = pl.off_x + round_up((size_t)M * N * 4, 256);
   } else {
     pl.ws = 0;
@@ -151,6 +154,55 @@ int pick_big(int idx, int64_t M, int64_t N, int64_t K, int in_f32, int loop, int
   return rounds(256, 256) * (1.4 * kt + 12.0) < rounds(128, tn) * (step * kt + 4.0) ? big : idx;
 }
 
+// Time (us) of the GEMM part of a plan on 128-row tiles or, for row clusters
+// and plain stores, on small tiles, up to what both have in common.  Rounds of
+// one workgroup per CU; a round costs its start and store (4) plus, for the
+// 128-row tiles, its 128-byte k stages (bf16 as in pick_big; the register-staged
+// loop about twice that; fp32, bound by its MFMAs, 2.2 per 128 columns), for the
+// small ones the operand bytes one workgroup streams or its fp32 MFMAs.
+double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch) {
+  const GemmKernel& t = gemm_kernel(idx);
+  const int64_t wgs = (M + 127) / 128 * ((N + t.tn - 1) / t.tn) * batch, tk = t.in_f32 ? 32 : 64;
+  double step = t.in_f32 ? 2.2 * t.tn / 128 : t.tn == 256 ? 0.9 : t.tn == 192 ? 0.77 : 0.55;
+  if (t.loop == 0) step *= 2.0;
+  return (double)((wgs + kAssumedCUs - 1) / kAssumedCUs) * (step * (double)((K + tk - 1) / tk) + 4.0);
+}
+double cost_small(const GemmKernel& t, int64_t rounds, int64_t wgs, int64_t K) {
+  const double esz = t.in_f32 ? 4.0 : 2.0;
+  // bytes per us: a 32 x 32 tile's workgroups slow each other down when many
+  const double rate = t.tm + t.tn > 64 || wgs <= 64 ? 90e3 : 50e3;
+  const double stream = (double)(t.tm + t.tn) * (double)K * esz / rate;
+  const double mfma = t.in_f32 ? 2.0 * t.tm * t.tn * (double)K / 0.5e6 : 0.0;
+  return (double)rounds * (4.0 + std::max(stream, mfma));
+}
+
+// The small tile (32 x 32, 32 x 64, 64 x 64) of least cost if that is below
+// `limit`, else -1.  cluster: its column tiles must divide N into at most 32
+// peers, whose row blocks run in rounds of the groups resident on an XCD (32
+// CUs).  Measured post-norms (us, this tile against the 128-row one): 32 x 1024 x
+// 1024 9.0 / 14.6, 333 x 768 x 3072 14.1 / 26.9, 1024 x 1024 x 1024 13.6 / 15.8,
+// 128 x 768 x 768 in fp32 12.5 / 57.7; past one round it loses: 2048 x 1024 x
+// 1024 22.9 / 16.2.  Plain products with their row pass: 16 x 4096 x 4096 17.9 /
+// 35.6, 256 x 4096 x 4096 23.1 / 41.4, 1024 x 4096 x 4096 69 / 49.
+int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int64_t batch, bool cluster, double limit) {
+  int best = -1;
+  for (const auto& tile : {std::pair<int, int>{32, 32}, {32, 64}, {64, 64}}) {
+    const int idx = find_gemm_kernel(in_f32, tile.first, tile.second, w_nk ? 1 : 2, 3);
+    if (idx < 0) continue;
+    const int64_t rb = (M + tile.first - 1) / tile.first, cn = (N + tile.second - 1) / tile.second;
+    const int64_t wgs = rb * cn * batch;
+    int64_t rounds = (wgs + kAssumedCUs - 1) / kAssumedCUs;
+    if (cluster) {
+      if (N % tile.second != 0 || cn > kSmallMaxPeers || kArriveUnit % (unsigned long long)cn != 0) continue;
+      const int64_t groups = 8 * std::min<int64_t>(kMaxSlots / 8, kAssumedCUs / 8 / cn);
+      rounds = (rb + groups - 1) / groups;
+    }
+    const double c = cost_small(gemm_kernel(idx), rounds, wgs, K);
+    if (c < limit) { limit = c; best = idx; }
+  }
+  return best;
+}
+
 // Chooses kernel and row path for a GEMM (+ row subgraph).  `epi` selects the
 // epilogue: 0 = plain (alpha, bias, store), 1 = row subgraph.  `need_rows` is
 // true when the subgraph has a row reduction (then rows must be completed
@@ -167,13 +219,22 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
   // Direct-to-LDS ring when K fills whole stages: W stored N x K (loop 1), or
   // bf16 W stored K x N with N a multiple of 8 (loop 2, transposing reads).
   const int loop = K % tk != 0 ? 0 : w_nk ? 1 : (!in_f32 && N % 8 == 0) ? 2 : 0;
+  // 128-row tile of the direct-to-LDS ring, or of the register-staged loop
+  auto tile_128 = [&](int ep, bool divides, int max_cn) {
+    const int idx = pick_tile(M, N, K, in_f32, loop, ep, divides, max_cn);
+    return idx >= 0 ? idx : pick_tile(M, N, K, in_f32, 0, ep, divides, max_cn);
+  };
   if (!need_rows) {
-    pl.kidx = pick_tile(M, N, K, in_f32, loop, epi, false, 0);
-    if (pl.kidx < 0) pl.kidx = pick_tile(M, N, K, in_f32, 0, epi, false, 0);
-    if (pl.kidx >= 0 && epi == 0) pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, batch);
+    pl.kidx = tile_128(epi, false, 0);
     pl.mode = ROWS_LOCAL;
+    if (pl.kidx >= 0) {
+      const int small = pick_small(M, N, K, in_f32, w_nk, batch, false, cost_128(pl.kidx, M, N, K, batch));
+      if (small >= 0) pl.kidx = small;
+      else if (epi == 0) pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, batch);
+    }
   } else {
-    if (path == PATH_AUTO) {
+    const bool automatic = path == PATH_AUTO;
+    if (automatic) {
       // Row clusters when N splits into <= kAutoClusterPeers tiles; whole rows
       // instead when N is narrow and they give more workgroups (small M);
       // else split-N.  Every tile's exchange waits for the slowest of its
@@ -181,8 +242,7 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
       // round trip of x, so wide rows go to split-N unless a caller asks
       // for the cluster path.
       path = PATH_SPLIT;
-      int ck = pick_tile(M, N, K, in_f32, loop, 1, true, kAutoClusterPeers);
-      if (ck < 0) ck = pick_tile(M, N, K, in_f32, 0, 1, true, kAutoClusterPeers);
+      const int ck = tile_128(1, true, kAutoClusterPeers);
       if (ck >= 0) {
         path = PATH_CLUSTER;
         const GemmKernel& t = gemm_kernel(ck);
@@ -205,20 +265,34 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
         }
       pl.mode = ROWS_LOCAL;
     } else if (path == PATH_CLUSTER) {
-      pl.kidx = pick_tile(M, N, K, in_f32, loop, 1, true, kClusterMaxPeers);
-      if (pl.kidx < 0) pl.kidx = pick_tile(M, N, K, in_f32, 0, 1, true, kClusterMaxPeers);
+      pl.kidx = tile_128(1, true, kClusterMaxPeers);
       if (pl.kidx < 0)
         return fail(CF_ERR_UNSUPPORTED, "cluster path: no tile width divides N = %lld into <= %d peers",
                     (long long)N, kClusterMaxPeers);
       pl.mode = ROWS_CLUSTER;
     } else if (path == PATH_SPLIT) {
-      pl.kidx = pick_tile(M, N, K, in_f32, loop, 2, false, 0);
-      if (pl.kidx < 0) pl.kidx = pick_tile(M, N, K, in_f32, 0, 2, false, 0);
-      if (pl.kidx >= 0) pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, 1);
+      pl.kidx = tile_128(2, false, 0);
       pl.mode = ROWS_SPLIT;
     } else {
       return fail(CF_ERR_UNSUPPORTED, "unknown path %d", path);
     }
+    // Fewer rows than fill the chip with 128-row tiles: small tiles, as a row
+    // cluster or (row pass and second launch included: 4 us) as the plain
+    // product of the split path.  Only where the automatic choice already
+    // takes a workspace, and not under an explicit path.
+    if (automatic && pl.kidx >= 0 && pl.mode != ROWS_LOCAL) {
+      const double now = cost_128(pl.kidx, M, N, K, 1) + (pl.mode == ROWS_SPLIT ? 4.0 : 0.0);
+      const int sc = allow_cluster ? pick_small(M, N, K, in_f32, w_nk, 1, true, now) : -1;
+      const int sp = sc < 0 && pl.mode == ROWS_SPLIT ? pick_small(M, N, K, in_f32, w_nk, 1, false, now - 4.0) : -1;
+      if (sc >= 0) {
+        pl.kidx = sc;
+        pl.mode = ROWS_CLUSTER;
+      } else if (sp >= 0) {
+        pl.kidx = sp;
+      }
+    }
+    if (pl.kidx >= 0 && pl.mode == ROWS_SPLIT && gemm_kernel(pl.kidx).epi == 2)
+      pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, 1);
   }
   if (pl.kidx < 0) return fail(CF_ERR_UNSUPPORTED, "no compiled tile for this shape");
   const GemmKernel& t = gemm_kernel(pl.kidx);
@@ -235,9 +309,9 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     pl.slots = std::min(pl.slots, std::min(slots, kMaxSlots / 8));
   }
   // the finish pass reads a row's partials one per lane of a 64-lane wave
-  if (pl.mode == ROWS_SPLIT && pl.cn > 64)
+  if (pl.mode == ROWS_SPLIT && t.epi == 2 && pl.cn > 64)
     return fail(CF_ERR_UNSUPPORTED, "split path: %d tiles per row exceed 64", pl.cn);
-  if (pl.mode == ROWS_CLUSTER && (pl.tm > kRecRows || pl.cn > kRecPeers))
+  if (pl.mode == ROWS_CLUSTER && (t.epi == 3 ? pl.tm * pl.cn > kRecRows * kRecPeers : pl.tm > kRecRows || pl.cn > kRecPeers))
     return fail(CF_ERR_UNSUPPORTED, "cluster path: tile of %d rows x %d peers exceeds the exchange records",
                 pl.tm, pl.cn);
   size_workspace(pl, M, N, allow_cluster);
@@ -275,7 +349,7 @@ cf_status run_rows(const Plan& pl, GemmRowsParams p, void* ws, hipStream_t st) {
     f.ldp = p.N;
     f.p_f32 = 1;
     f.epi = full;
-    if (gemm_kernel(pl.kidx).epi == 0) {
+    if (gemm_kernel(pl.kidx).epi != 2) {
       // The plain product in fp32; the row pass runs every stage (it reads the
       // residual and takes the statistics of the rows it holds).
       f.rows_per_batch = p.M;

@@ -14,7 +14,7 @@ static std::vector<GemmKernel>& table() {
   static std::once_flag once;
   std::call_once(once, [] {
     for (auto get : {gemm_kernels_v2, gemm_kernels_v1, gemm_kernels_wr, gemm_kernels_split, gemm_kernels_kn,
-                     gemm_kernels_big}) {
+                     gemm_kernels_big, gemm_kernels_small}) {
       int n = 0;
       const GemmKernel* k = get(&n);
       t.insert(t.end(), k, k + n);
@@ -55,9 +55,13 @@ int resident_wgs(int idx) {
 
 hipError_t launch_gemm_rows(const GemmRowsParams& p, int idx, hipStream_t st) {
   const GemmKernel& k = table()[idx];
-  // 256-row tiles have one workgroup per tile; the others a whole number of
-  // row-block slots on each XCD.
-  dim3 grid(k.tm == 256 ? (unsigned)(p.num_rb * p.cn) : (unsigned)(8 * p.slots * p.cn), (unsigned)p.batch);
+  // 256-row tiles have one workgroup per tile, small tiles without row clusters
+  // a whole number of column tiles on each XCD, the others a whole number of
+  // row-block slots.
+  unsigned wgs = (unsigned)(8 * p.slots * p.cn);
+  if (k.tm == 256) wgs = (unsigned)(p.num_rb * p.cn);
+  else if (k.epi == 3 && p.mode != ROWS_CLUSTER) wgs = (unsigned)(8 * ((p.cn + 7) / 8) * p.num_rb);
+  dim3 grid(wgs, (unsigned)p.batch);
   dim3 block((unsigned)k.threads);
   void* args[] = {const_cast<GemmRowsParams*>(&p)};
   // Without row clusters every tile has a workgroup of its own (grouped

@@ -124,6 +124,7 @@ const GemmKernel* gemm_kernels_wr(int* n);     // whole-row tiles (register-stag
 const GemmKernel* gemm_kernels_split(int* n);  // split-N GEMM pass (both main loops)
 const GemmKernel* gemm_kernels_kn(int* n);     // direct-to-LDS pipeline, bf16 W stored K x N
 const GemmKernel* gemm_kernels_big(int* n);    // 256 x 256 tiles, plain epilogue
+const GemmKernel* gemm_kernels_small(int* n);  // 32 / 64-row tiles, split K in the workgroup, any epilogue (epi 3)
 int find_gemm_kernel(int in_f32, int tm, int tn, int loop, int epi);   // -1 if none
 const GemmKernel& gemm_kernel(int idx);
 int resident_wgs(int idx);   // co-resident workgroups of this kernel on the device

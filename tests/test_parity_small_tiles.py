@@ -1,0 +1,130 @@
+"""GPU parity of the small tiles (32 x 32, 32 x 64, 64 x 64, split K inside the
+workgroup) that the automatic path takes for few rows, against the fp64 oracle:
+row clusters of up to 32 peers, the plain product of the split path, and plain
+products, at the edges of tiles, of K stages and of the row count."""
+import numpy as np
+import pytest
+
+from oracle import comfuse_oracle as O
+from paper_2608_03537_amd import inputs as I
+from tests.helpers import assert_close_bf16, assert_close_f32, dev, host
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("no GPU", allow_module_level=True)
+
+from paper_2608_03537_amd import comfuse as cf  # noqa: E402
+
+LAYOUT = {"nk": cf.CF_LAYOUT_NK, "kn": cf.CF_LAYOUT_KN}
+
+
+def _chain(inp, layout, dtype, kind):
+    """One subgraph call on the automatic path and the oracle's result."""
+    X, W = dev(inp.X, dtype), dev(I.lay_out_weight(inp.W, layout), dtype)
+    vec = lambda v: dev(v, "f32")
+    out = torch.float32 if dtype == "f32" else torch.bfloat16
+    Y = torch.empty((inp.M, inp.N), dtype=out, device="cuda")
+    store = dict(kind=cf.CF_N_STORE, out=Y, ld=inp.N, dtype=cf._dt(Y))
+    x = O.matmul(inp.X, inp.W)
+    if kind == "ln":
+        R = dev(inp.R, dtype)
+        spec = [dict(kind=cf.CF_N_SCALE, f0=0.5), dict(kind=cf.CF_N_BIAS, v0=vec(inp.bias)),
+                dict(kind=cf.CF_N_RESIDUAL, ld=inp.N, dtype=cf._dt(R), **{"in": R}),
+                dict(kind=cf.CF_N_LAYERNORM, v0=vec(inp.gamma), v1=vec(inp.beta), f0=1e-5), store]
+        ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, inp.gamma, inp.beta, 0.5, 1e-5)
+    elif kind == "rms":
+        spec = [dict(kind=cf.CF_N_BIAS, v0=vec(inp.bias)), dict(kind=cf.CF_N_RMSNORM, v0=vec(inp.gamma), f0=1e-5),
+                store]
+        ref = O.rmsnorm(O.bias_residual(x, inp.bias), inp.gamma, 1e-5)
+    else:
+        spec = [dict(kind=cf.CF_N_SCALE, f0=8.0), dict(kind=cf.CF_N_SOFTCAP, f0=10.0), dict(kind=cf.CF_N_SOFTMAX),
+                store]
+        ref = O.softmax_rows(10.0 * np.tanh(8.0 * x / 10.0))
+    cf.gemm_subgraph(X, W, spec, w_layout=LAYOUT[layout])
+    torch.cuda.synchronize()
+    return host(Y), ref
+
+
+@pytest.mark.parametrize("kind", ["ln", "rms", "msts"])
+@pytest.mark.parametrize("layout,dtype", [("nk", "bf16"), ("kn", "bf16"), ("nk", "f32")])
+@pytest.mark.parametrize("M,K,N", [
+    (1, 512, 512),      # one row
+    (33, 1040, 1024),   # one row past a tile, K a quarter stage past whole stages, 32 or 16 peers
+    (65, 48, 768),      # less than one stage: three waves have no k
+    (300, 272, 640),    # 32 x 64 tiles, an odd number of stages per wave
+    (1000, 528, 768),   # 64 x 64 tiles, ragged last row block
+])
+def test_row_clusters(M, K, N, layout, dtype, kind):
+    inp = I.postnorm_inputs(M, K, N, dtype, seed=51, bias_std=0.5, gamma="uniform", beta_std=0.3)
+    got, ref = _chain(inp, layout, dtype, kind)
+    (assert_close_f32 if dtype == "f32" else assert_close_bf16)(got, ref, f"{kind} {M}x{K}x{N} {layout} {dtype}")
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("M,N", [(40, 1024),    # cluster of 32 or 16 peers, two exchanges
+                                 (129, 2048),   # cluster of 32 peers
+                                 (70, 4128)])   # split path: plain product with a ragged last column tile
+def test_quant_chain(M, N, layout):
+    inp = I.postnorm_inputs(M, 1040, N, "bf16", seed=52, with_affine=False)
+    X, W, R = dev(inp.X), dev(I.lay_out_weight(inp.W, layout)), dev(inp.R)
+    Z, s, Q = cf.ln_gelu_amax(X, W, dev(inp.bias, "f32"), R, eps=inp.eps, z_dtype=torch.float32,
+                              w_layout=LAYOUT[layout])
+    torch.cuda.synchronize()
+    z, _, _ = O.ln_gelu_amax(inp.X, inp.W, inp.bias, inp.R, eps=inp.eps)
+    assert_close_f32(host(Z), z, f"Z {M}x{N}")
+    s32, q32 = O.rowamax_quant_f32(host(Z).astype(np.float32))
+    assert np.array_equal(s.cpu().numpy(), s32)
+    assert np.array_equal(Q.cpu().numpy(), q32)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("batch,M,K,N", [(1, 17, 2064, 96), (1, 30, 784, 800), (3, 33, 1040, 160), (1, 1, 16, 32),
+                                         (1, 515, 528, 1056)])
+def test_plain_products(batch, M, K, N, layout, dtype):
+    rng = np.random.default_rng(53)
+    rnd = lambda *sh: (lambda v: I.round_to_bf16(v) if dtype == "bf16" else v)(rng.standard_normal(sh).astype(np.float32))
+    A, B = rnd(batch, M, K), rnd(batch, K, N) / np.float32(np.sqrt(K) if dtype == "f32" else 2.0 ** 5)
+    bias = rng.standard_normal(N).astype(np.float32)
+    Bd = np.stack([I.lay_out_weight(b, layout) for b in B])
+    C = cf.gemm(dev(A, dtype), dev(Bd, dtype), b_layout=LAYOUT[layout], bias=dev(bias, "f32"), alpha=0.5,
+                out_dtype=torch.float32)
+    torch.cuda.synchronize()
+    for b in range(batch):
+        assert_close_f32(host(C[b]), 0.5 * O.matmul(A[b], B[b]) + bias, f"{M}x{K}x{N} {layout} {dtype}")
+
+
+def test_calls_of_all_tiles_share_a_workspace():
+    """Row clusters of 32-, 64- and 128-row tiles through one workspace: their records lie differently in a slot's
+    area, and each exchange must accept its own round's only."""
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+    for M, N, path in [(300, 768, 0), (1024, 1024, 2), (1000, 1024, 0), (40, 1024, 0), (2048, 768, 2), (700, 512, 0),
+                       (40, 2048, 0), (300, 768, 0)]:
+        inp = I.postnorm_inputs(M, 256, N, "bf16", seed=M + N, with_affine=False)
+        got = []
+        for _ in range(2):
+            Y = cf.gemm_postnorm(dev(inp.X), dev(I.lay_out_weight(inp.W, "nk")), dev(inp.bias, "f32"), dev(inp.R),
+                                 eps=inp.eps, path=path, ws=ws)
+            torch.cuda.synchronize()
+            got.append(host(Y))
+        assert np.array_equal(got[0], got[1])
+        assert_close_bf16(got[0], O.postnorm(inp.X, inp.W, inp.bias, inp.R, None, None, 1.0, inp.eps), f"{M}x{N}")
+
+
+def test_peer_wait_failure_is_reported():
+    """With the sticky word set beforehand every wait gives up at its next poll, and the check reports it."""
+    inp = I.postnorm_inputs(200, 256, 768, "bf16", seed=54)
+    args = (dev(inp.X), dev(I.lay_out_weight(inp.W, "nk")), dev(inp.bias, "f32"), dev(inp.R), dev(inp.gamma, "f32"),
+            dev(inp.beta, "f32"))
+    ws = torch.zeros(cf.cf_gemm_postnorm_workspace(cf.postnorm_args(*args, Y=torch.empty_like(args[3]))),
+                     dtype=torch.uint8, device="cuda")
+    ws.view(torch.int32)[0] = 1
+    cf.gemm_postnorm(*args, eps=inp.eps, ws=ws, check=False)
+    with pytest.raises(cf.CfError, match="PEER_TIMEOUT"):
+        cf.check_workspace(ws)
+    Y = cf.gemm_postnorm(*args, eps=inp.eps, ws=ws)
+    torch.cuda.synchronize()
+    ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, inp.gamma, inp.beta, 1.0, inp.eps)
+    assert_close_bf16(host(Y), ref, "after a reported failure")
