@@ -154,50 +154,67 @@ int pick_big(int idx, int64_t M, int64_t N, int64_t K, int in_f32, int loop, int
   return rounds(256, 256) * (1.4 * kt + 12.0) < rounds(128, tn) * (step * kt + 4.0) ? big : idx;
 }
 
-// Time (us) of the GEMM part of a plan on 128-row tiles or, for row clusters
-// and plain stores, on small tiles, up to what both have in common.  Rounds of
-// one workgroup per CU; a round costs its start and store (4) plus, for the
-// 128-row tiles, its 128-byte k stages (bf16 as in pick_big; the register-staged
-// loop about twice that; fp32, bound by its MFMAs, 2.2 per 128 columns), for the
-// small ones the operand bytes one workgroup streams or its fp32 MFMAs.
-double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch) {
-  const GemmKernel& t = gemm_kernel(idx);
-  const int64_t wgs = (M + 127) / 128 * ((N + t.tn - 1) / t.tn) * batch, tk = t.in_f32 ? 32 : 64;
-  double step = t.in_f32 ? 2.2 * t.tn / 128 : t.tn == 256 ? 0.9 : t.tn == 192 ? 0.77 : 0.55;
-  if (t.loop == 0) step *= 2.0;
-  return (double)((wgs + kAssumedCUs - 1) / kAssumedCUs) * (step * (double)((K + tk - 1) / tk) + 4.0);
+// Estimated time (us) of `wgs` workgroups of a kernel in `rounds` rounds, up to
+// what all kernels have in common; used to choose between 128-row tiles, 64 x
+// 128 row clusters and small tiles.  A round costs its 64-deep k steps (the
+// small tiles' grow with the number of CUs that stream at once) and its start
+// and epilogue; a row cluster's first round starts under the launch.  Fitted to
+// post-norms and plain products of 1 to 4096 rows, N 512 to 4096, K 512 to 4096.
+double plan_cost(const GemmKernel& t, int64_t rounds, int64_t wgs, int64_t K, bool cluster) {
+  const double kt = (double)((K + 63) / 64), busy = std::min(1.0, (double)wgs / kAssumedCUs);
+  double step, start;
+  if (t.epi == 3) {   // small tiles: operand stream, or fp32 MFMAs (0.42 TFLOP/s a CU)
+    step = t.tm == 64 ? 0.13 + 0.07 * busy : t.tn == 64 ? 0.115 + 0.065 * busy : 0.10 + 0.09 * busy;
+    if (t.in_f32) step = std::max(2.0 * step, 2.0 * t.tm * t.tn * 64 / 0.42e6);
+    start = cluster ? (t.tm == 64 ? 8.0 : 6.0) : t.in_f32 ? 5.0 : t.tm == 64 ? 4.0 : 3.0;
+  } else if (t.tm == 64) {
+    step = 0.31;
+    start = 6.0;
+  } else {            // the register-staged loop takes longer than the ring
+    step = (t.in_f32 ? 4.4 : 0.4) * t.tn / 128 * (t.loop != 0 ? 1.0 : t.in_f32 ? 1.2 : 2.0);
+    start = cluster ? 8.0 : 6.0;
+  }
+  const double c = (double)rounds * (step * kt + start);
+  if (cluster) return c - 4.0;
+  // several rounds of small tiles were measured up to 15 % over the estimate
+  return t.epi == 3 && rounds > 1 ? 1.15 * c : c;
 }
-double cost_small(const GemmKernel& t, int64_t rounds, int64_t wgs, int64_t K) {
-  const double esz = t.in_f32 ? 4.0 : 2.0;
-  // bytes per us: a 32 x 32 tile's workgroups slow each other down when many
-  const double rate = t.tm + t.tn > 64 || wgs <= 64 ? 90e3 : 50e3;
-  const double stream = (double)(t.tm + t.tn) * (double)K * esz / rate;
-  const double mfma = t.in_f32 ? 2.0 * t.tm * t.tn * (double)K / 0.5e6 : 0.0;
-  return (double)rounds * (4.0 + std::max(stream, mfma));
+double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch, bool cluster) {
+  const GemmKernel& t = gemm_kernel(idx);
+  const int64_t wgs = (M + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn) * batch;
+  return plan_cost(t, (wgs + kAssumedCUs - 1) / kAssumedCUs, wgs, K, cluster);
 }
 
-// The small tile (32 x 32, 32 x 64, 64 x 64) of least cost if that is below
-// `limit`, else -1.  cluster: its column tiles must divide N into at most 32
-// peers, whose row blocks run in rounds of the groups resident on an XCD (32
-// CUs).  Measured post-norms (us, this tile against the 128-row one): 32 x 1024 x
-// 1024 9.0 / 14.6, 333 x 768 x 3072 14.1 / 26.9, 1024 x 1024 x 1024 13.6 / 15.8,
-// 128 x 768 x 768 in fp32 12.5 / 57.7; past one round it loses: 2048 x 1024 x
-// 1024 22.9 / 16.2.  Plain products with their row pass: 16 x 4096 x 4096 17.9 /
-// 35.6, 256 x 4096 x 4096 23.1 / 41.4, 1024 x 4096 x 4096 69 / 49.
-int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int64_t batch, bool cluster, double limit) {
+// The kernel of least cost among the small tiles (32 x 32, 32 x 64, 64 x 64) and,
+// for row clusters on the direct-to-LDS ring (loop 1, 2), the 64 x 128 tile, if
+// that is below `limit`; else -1.  cluster: column tiles must divide N into at
+// most 32 (64 x 128: 16) peers, whose row blocks run in rounds of the groups
+// resident on an XCD (32 CUs).  Measured post-norms (us; 32 x 64 / 64 x 64 / 64 x
+// 128 / 128 x 128): 333 x 768 x 3072 14.1 / 17.8 / - / 26.9; 1024 x 1024 x 1024
+// 17.4 / 13.6 / 12.1 / 15.8; 2048 x 1024 x 1024 30 / 22.9 / 13.2 / 16.2; 1536 x
+// 768 x 3072 36 / 32.7 / 21.1 / 27.0; two rounds of 64 x 128 lose (3072 x 1024 x
+// 1024 23.0 / 17.2); fp32 128 x 768 x 768 15.2 / 21.9 / - / 57.7.  Plain products
+// with their row pass: 16 x 4096 x 4096 17.9 / 20.9 against 35.6, 256 rows 30.1 /
+// 23.1 against 41.4, 1024 rows 106 / 69 against 49.
+int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop, int64_t batch, bool cluster,
+               double limit) {
   int best = -1;
-  for (const auto& tile : {std::pair<int, int>{32, 32}, {32, 64}, {64, 64}}) {
-    const int idx = find_gemm_kernel(in_f32, tile.first, tile.second, w_nk ? 1 : 2, 3);
-    if (idx < 0) continue;
-    const int64_t rb = (M + tile.first - 1) / tile.first, cn = (N + tile.second - 1) / tile.second;
+  struct { int tm, tn, loop, epi, peers; } const tiles[] = {
+      {32, 32, w_nk ? 1 : 2, 3, kSmallMaxPeers}, {32, 64, w_nk ? 1 : 2, 3, kSmallMaxPeers},
+      {64, 64, w_nk ? 1 : 2, 3, kSmallMaxPeers}, {64, 128, loop, 1, kClusterMaxPeers}};
+  for (const auto& t : tiles) {
+    if (t.epi == 1 && (!cluster || loop < 1)) continue;
+    const int idx = find_gemm_kernel(in_f32, t.tm, t.tn, t.loop, t.epi);
+    if (idx < 0 || (t.epi == 1 && K / 64 < gemm_kernel(idx).stages - 1)) continue;
+    const int64_t rb = (M + t.tm - 1) / t.tm, cn = (N + t.tn - 1) / t.tn;
     const int64_t wgs = rb * cn * batch;
     int64_t rounds = (wgs + kAssumedCUs - 1) / kAssumedCUs;
     if (cluster) {
-      if (N % tile.second != 0 || cn > kSmallMaxPeers || kArriveUnit % (unsigned long long)cn != 0) continue;
+      if (N % t.tn != 0 || cn > t.peers || kArriveUnit % (unsigned long long)cn != 0) continue;
       const int64_t groups = 8 * std::min<int64_t>(kMaxSlots / 8, kAssumedCUs / 8 / cn);
       rounds = (rb + groups - 1) / groups;
     }
-    const double c = cost_small(gemm_kernel(idx), rounds, wgs, K);
+    const double c = plan_cost(gemm_kernel(idx), rounds, wgs, K, cluster);
     if (c < limit) { limit = c; best = idx; }
   }
   return best;
@@ -228,7 +245,8 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     pl.kidx = tile_128(epi, false, 0);
     pl.mode = ROWS_LOCAL;
     if (pl.kidx >= 0) {
-      const int small = pick_small(M, N, K, in_f32, w_nk, batch, false, cost_128(pl.kidx, M, N, K, batch));
+      const int small = pick_small(M, N, K, in_f32, w_nk, loop, batch, false,
+                                   cost_128(pl.kidx, M, N, K, batch, false));
       if (small >= 0) pl.kidx = small;
       else if (epi == 0) pl.kidx = pick_big(pl.kidx, M, N, K, in_f32, loop, batch);
     }
@@ -276,14 +294,15 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     } else {
       return fail(CF_ERR_UNSUPPORTED, "unknown path %d", path);
     }
-    // Fewer rows than fill the chip with 128-row tiles: small tiles, as a row
-    // cluster or (row pass and second launch included: 4 us) as the plain
-    // product of the split path.  Only where the automatic choice already
+    // Fewer rows than fill the chip with 128-row tiles: 64 x 128 or small tiles,
+    // as a row cluster or (row pass and second launch: about 4 us) small ones as
+    // the plain product of the split path.  Only where the automatic choice already
     // takes a workspace, and not under an explicit path.
     if (automatic && pl.kidx >= 0 && pl.mode != ROWS_LOCAL) {
-      const double now = cost_128(pl.kidx, M, N, K, 1) + (pl.mode == ROWS_SPLIT ? 4.0 : 0.0);
-      const int sc = allow_cluster ? pick_small(M, N, K, in_f32, w_nk, 1, true, now) : -1;
-      const int sp = sc < 0 && pl.mode == ROWS_SPLIT ? pick_small(M, N, K, in_f32, w_nk, 1, false, now - 4.0) : -1;
+      const double now = cost_128(pl.kidx, M, N, K, 1, pl.mode == ROWS_CLUSTER);
+      const int sc = !allow_cluster ? -1 : pick_small(M, N, K, in_f32, w_nk, loop, 1, true,
+                                                      pl.mode == ROWS_SPLIT ? now + 4.0 : now);
+      const int sp = sc < 0 && pl.mode == ROWS_SPLIT ? pick_small(M, N, K, in_f32, w_nk, loop, 1, false, now) : -1;
       if (sc >= 0) {
         pl.kidx = sc;
         pl.mode = ROWS_CLUSTER;

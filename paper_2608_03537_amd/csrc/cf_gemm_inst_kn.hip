@@ -6,9 +6,11 @@ namespace cf {
 
 using S0 = TileShape<bf16_t, 2, 2, 2, 2, 128, 4>;
 using S2 = TileShape<bf16_t, 2, 4, 2, 2, 128, 3>;
+using S5 = TileShape<bf16_t, 1, 2, 2, 2, 128, 4>;   // 64 x 128, row clusters
 
 static const GemmKernel kTable[] = {
     CF_GEMM_ENTRY(S0, 2, 0), CF_GEMM_ENTRY(S0, 2, 1), CF_GEMM_ENTRY(S0, 2, 2),
+    CF_GEMM_ENTRY(S5, 2, 1),
     CF_GEMM_ENTRY(S2, 2, 0), CF_GEMM_ENTRY(S2, 2, 1), CF_GEMM_ENTRY(S2, 2, 2),
 };
 

@@ -1478,12 +1478,12 @@ void gemm_rows_kernel(GemmRowsParams p) {
   }
 }
 
-// The persistent form of an instantiation: only 128-row tiles with the row
-// subgraph run the row-cluster path; every other entry runs one tile per
+// The persistent form of an instantiation: only 128- and 64-row tiles with the
+// row subgraph run the row-cluster path; every other entry runs one tile per
 // workgroup and names its one-tile kernel again.
 template <class S, int LOOP, int EPI>
 inline const void* gemm_persist_fn() {
-  if constexpr (EPI == 1 && S::TM == 128) return reinterpret_cast<const void*>(&gemm_rows_kernel<S, LOOP, EPI, true>);
+  if constexpr (EPI == 1 && S::TM >= 64) return reinterpret_cast<const void*>(&gemm_rows_kernel<S, LOOP, EPI, true>);
   else return reinterpret_cast<const void*>(&gemm_rows_kernel<S, LOOP, EPI, false>);
 }
 
