@@ -435,6 +435,234 @@ void b2b_ffn_kernel(B2BParams p) {
                                      p.M, D, m0, 0, smem, tid, lane, pr, h);
 }
 
+// ---------------------------------------------------------------------------
+// Few rows.  The 128-row kernel above gives one workgroup per 128 rows, whose
+// rounds are a serial chain of weight loads, products and barriers (about 2 us
+// each) that most of the chip watches.  Here a workgroup owns 32 rows and its
+// four waves split the hidden units: wave w takes units (of 64) w, w + 4, ... and
+// runs both products for them on its own, so there is no barrier until the
+// partial O tiles are added through LDS in wave order.  The weights stream
+// through a ring of S stages per wave, each stage 64 rows x 128 bytes (whole
+// lines): per unit D / 64 stages of W1^T (64 hidden rows, 64 k each), then D / 64
+// of W2^T (64 output rows, the unit's 64 hidden each).  Every workgroup reads all
+// weights, so what bounds it is the CU's load path (512 KB at N1 = 512, D = 256:
+// about 7 us).  The register hand-off of S is the 128-row kernel's.
+// ---------------------------------------------------------------------------
+template <int N1, int D>
+struct FfnRows {
+  static constexpr int TM = 32, NW = 4, NT = 64 * NW, S = 4;
+  static constexpr int UNITS = N1 / 64, UPW = (UNITS + NW - 1) / NW;   // units: all, per wave
+  static constexpr int DB = D / 64, SPU = 2 * DB;                      // stages per unit
+  static constexpr int STAGE = 64 * 128, RING = S * STAGE;
+  static constexpr int PITCH = D * 4 + 16;                             // row of a partial O tile
+  static constexpr int LDS = NW * RING > NW * TM * PITCH ? NW * RING : NW * TM * PITCH;
+  static_assert(N1 % 64 == 0 && D % 64 == 0 && LDS <= 160 * 1024, "shape");
+};
+
+template <int N1, int D>
+__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void b2b_ffn_rows_kernel(B2BParams p) {
+  using F = FfnRows<N1, D>;
+  __shared__ __attribute__((aligned(16))) char smem[F::LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lg = lane >> 5;
+  const int bz = blockIdx.y, m0 = blockIdx.x * F::TM;
+  const bf16_t* X = p.X + (int64_t)bz * p.sx;
+  const char* W1 = reinterpret_cast<const char*>(p.W1 + (int64_t)bz * p.sw1);
+  const char* W2 = reinterpret_cast<const char*>(p.W2 + (int64_t)bz * p.sw2);
+  const int units = wave < F::UNITS ? (F::UNITS - wave + F::NW - 1) / F::NW : 0;   // of this wave
+  const int n_st = units * F::SPU;
+
+  // X^T fragments: xf[ks] = X[m][16 ks + 8 lg .. +8].
+  u32x4_t xf[D / 16];
+  {
+    const bf16_t* xr = X + (int64_t)min(m0 + lr, p.M - 1) * p.ldx + 8 * lg;
+#pragma unroll
+    for (int ks = 0; ks < D / 16; ++ks) xf[ks] = gload16(xr + 16 * ks);
+  }
+  // b1 of the wave's hidden units, in accumulator order: elements 8 s .. 8 s + 7 of
+  // block bn hold hidden units 32 bn + 16 s + 8 lg + 0..7 of the unit.
+  f32x4_t b1v[F::UPW][2][2][2];
+#pragma unroll
+  for (int u = 0; u < F::UPW; ++u)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int h = min((wave + F::NW * u) * 64, N1 - 64) + 32 * (i >> 2) + 16 * ((i >> 1) & 1) + 8 * lg + 4 * (i & 1);
+      b1v[u][i >> 2][(i >> 1) & 1][i & 1] =
+          p.b1 ? *reinterpret_cast<const f32x4_t*>(p.b1 + h) : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    }
+
+  // Load j (8 rows) of stage st: row r = 8 j + lane / 8, 16-byte chunk c at
+  // position c ^ ((r >> 1) & 7) (conflict-free fragment reads).  The W1^T rows of
+  // each 32-row block are taken with bits 2 and 3 of the row swapped.
+  char* const ring = smem + wave * F::RING;
+  const uint32_t ring0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)ring);
+  const int r8 = lane >> 3, ch = (lane & 7) ^ (lane >> 4);
+  const int64_t p1 = 2 * p.ldw1, p2 = 2 * p.ldw2;
+  const int r8h = (r8 & 3) | ((r8 & 4) << 1);               // bit 2 of the row -> bit 3
+  const uint32_t l1 = (uint32_t)(r8h * p1), l2 = (uint32_t)(r8 * p2);
+  auto load = [&](int st, int j) {
+    const int u = wave + F::NW * (st / F::SPU), q = st % F::SPU;
+    const uint32_t c16 = (uint32_t)(ch ^ ((j & 1) << 2)) * 16;
+    char* dst = ring + (st % F::S) * F::STAGE + j * 1024;
+    if (q < F::DB) {   // rows 8 j .. of the unit: block j / 4, bit 3 of the row (j & 1) -> bit 2
+      const int row = 64 * u + 32 * (j >> 2) + 16 * ((j >> 1) & 1) + 4 * (j & 1);
+      dma16(W1 + row * p1 + 128 * q + (l1 + c16), dst);
+    } else {
+      dma16(W2 + (64 * (q - F::DB) + 8 * j) * p2 + 128 * u + (l2 + c16), dst);
+    }
+  };
+#pragma unroll
+  for (int st = 0; st < F::S; ++st)
+    if (st < n_st)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) load(st, j);
+
+  f32x16_t O[D / 32];
+#pragma unroll
+  for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) O[b][i] = 0.0f;
+  const int sw = (lr >> 1) & 7;
+  // Stage st (a unit's q-th): fragments into f, then the stage's slot takes stage
+  // st + S (its loads go between the MFMAs).
+  u32x4_t f[2][4];
+  auto open = [&](int st) {
+    const int after = n_st - 1 - st;   // stages issued after st: at most S - 1
+    if (after >= 3) wait_vmcnt<24>();
+    else if (after == 2) wait_vmcnt<16>();
+    else if (after == 1) wait_vmcnt<8>();
+    else wait_vmcnt<0>();
+    uint32_t a[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) a[ks] = ring0 + (st % F::S) * F::STAGE + lr * 128 + (((2 * ks + lg) ^ sw) << 4);
+    read_blocks(f, a);
+  };
+#pragma unroll
+  for (int ui = 0; ui < F::UPW; ++ui) {
+    if (ui >= units) break;
+    f32x16_t P[2];
+#pragma unroll
+    for (int bn = 0; bn < 2; ++bn)
+#pragma unroll
+      for (int s = 0; s < 2; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) P[bn][8 * s + e] = b1v[ui][bn][s][e >> 2][e & 3];
+#pragma unroll
+    for (int q = 0; q < F::DB; ++q) {   // P^T += W1^T X^T
+      const int st = ui * F::SPU + q;
+      open(st);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        Mma<bf16_t>::run(P[i & 1], f[i & 1][i >> 1], xf[4 * q + (i >> 1)]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + F::S < n_st) load(st + F::S, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    u32x4_t sf[4];                      // S = GELU(P + b1): k step 2 bn + s of the second product
+#pragma unroll
+    for (int bn = 0; bn < 2; ++bn) {
+#pragma unroll
+      for (int e = 0; e < 16; e += 4) {
+        GeluPipe gp;
+        const float x4[4] = {P[bn][e], P[bn][e + 1], P[bn][e + 2], P[bn][e + 3]};
+        float o4[4];
+#pragma unroll
+        for (int stg = 0; stg < 8; ++stg) gelu_stage(gp, x4, o4, stg);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) P[bn][e + q] = o4[q];
+      }
+      sf[2 * bn] = ffn_pack_step(P[bn], 0);
+      sf[2 * bn + 1] = ffn_pack_step(P[bn], 1);
+    }
+#pragma unroll
+    for (int q = 0; q < F::DB; ++q) {   // O^T += W2^T S^T, output rows 64 q .. +63
+      const int st = ui * F::SPU + F::DB + q;
+      open(st);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        Mma<bf16_t>::run(O[2 * q + (i & 1)], f[i & 1][i >> 1], sf[i >> 1]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + F::S < n_st) load(st + F::S, i);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+
+  // Residual and b2 of the lane's columns: row tid / 8, columns 64 g + 8 (tid % 8) + 0..7.
+  const int row = tid >> 3, tq = tid & 7, m = m0 + row;
+  const bool mv = m < p.M;
+  float x[F::DB][8];
+#pragma unroll
+  for (int g = 0; g < F::DB; ++g) {
+    const int n = 64 * g + 8 * tq;
+#pragma unroll
+    for (int q = 0; q < 8; q += 4) {
+      float r[4] = {0.0f, 0.0f, 0.0f, 0.0f}, b[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+      if (p.R && mv) load4<bf16_t>(p.R + (int64_t)bz * p.sr + (int64_t)m * p.ldr + n + q, r);
+      if (p.b2) load4<float>(p.b2 + n + q, b);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) x[g][q + i] = b[i] + r[i];
+    }
+  }
+  __syncthreads();   // every wave is done with its ring
+  {
+    char* part = smem + wave * F::TM * F::PITCH + lr * F::PITCH + 16 * lg;
+#pragma unroll
+    for (int b = 0; b < D / 32; ++b)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4_t*>(part + (32 * b + 8 * g) * 4) =
+            f32x4_t{O[b][4 * g], O[b][4 * g + 1], O[b][4 * g + 2], O[b][4 * g + 3]};
+  }
+  __syncthreads();
+  float t = 0.0f;
+#pragma unroll
+  for (int g = 0; g < F::DB; ++g)
+#pragma unroll
+    for (int q = 0; q < 8; q += 4) {
+      const char* src = smem + row * F::PITCH + (64 * g + 8 * tq + q) * 4;
+      f32x4_t s = *reinterpret_cast<const f32x4_t*>(src);
+#pragma unroll
+      for (int w = 1; w < F::NW; ++w) s += *reinterpret_cast<const f32x4_t*>(src + w * F::TM * F::PITCH);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) t += x[g][q + i] += s[i];
+    }
+  if (p.out_ln) {
+    const float mean = row_sum<8>(t) * (1.0f / D);
+    float d2 = 0.0f;
+#pragma unroll
+    for (int g = 0; g < F::DB; ++g)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        x[g][q] -= mean;
+        d2 = fmaf(x[g][q], x[g][q], d2);
+      }
+    const float rstd = rsqrtf(row_sum<8>(d2) * (1.0f / D) + p.eps);
+#pragma unroll
+    for (int g = 0; g < F::DB; ++g)
+#pragma unroll
+      for (int q = 0; q < 8; q += 4) {
+        const int n = 64 * g + 8 * tq + q;
+        float ga[4] = {1.0f, 1.0f, 1.0f, 1.0f}, be[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (p.gamma) load4<float>(p.gamma + n, ga);
+        if (p.beta) load4<float>(p.beta + n, be);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) x[g][q + i] = fmaf(x[g][q + i] * rstd, ga[i], be[i]);
+      }
+  }
+  if (!mv) return;
+#pragma unroll
+  for (int g = 0; g < F::DB; ++g) {
+    const u32x4_t o = {pack_bf16x2(x[g][0], x[g][1]), pack_bf16x2(x[g][2], x[g][3]), pack_bf16x2(x[g][4], x[g][5]),
+                       pack_bf16x2(x[g][6], x[g][7])};
+    __builtin_nontemporal_store(
+        o, reinterpret_cast<u32x4_t*>(p.O + (int64_t)bz * p.so + (int64_t)m * p.ldo + 64 * g + 8 * tq));
+  }
+}
+
 bool b2b_ffn_supported(int N1, int N2) {
   return (N1 == 512 && N2 == 256) || (N1 == 256 && N2 == 128) || (N1 == 128 && N2 == 64) ||
          (N1 == 256 && N2 == 256);
@@ -442,6 +670,17 @@ bool b2b_ffn_supported(int N1, int N2) {
 
 template <int N1, int D>
 static hipError_t launch_ffn(const B2BParams& p, hipStream_t st) {
+  // 32-row workgroups while they fit one generation of 256 CUs (each streams
+  // all weights), 128-row ones beyond.  Measured (us, N1 x D = 512 x 256, 256 x 256,
+  // 256 x 128, 128 x 64; this form / 128-row): 1 row 12.4 / 21.2, 8.9 / 13.7, 6.7 / 10.3, 4.8 /
+  // 6.3; 8192 rows 15.7 / 22.4, 11.6 / 15.1, 8.2 / 11.4, 5.8 / 7.0; 10000 rows 28.4 / 22.6,
+  // 20.8 / 15.1, 14.1 / 11.6, 9.2 / 6.7.
+  const int64_t row_blocks = (p.M + 31) / 32;
+  if (row_blocks * p.batch <= 256) {
+    hipLaunchKernelGGL((b2b_ffn_rows_kernel<N1, D>), dim3((unsigned)row_blocks, (unsigned)p.batch),
+                       dim3(FfnRows<N1, D>::NT), 0, st, p);
+    return hipGetLastError();
+  }
   using F = FfnShape<N1, D>;
   const dim3 grid((unsigned)((p.M + F::TM - 1) / F::TM), (unsigned)p.batch), block(F::NT);
   hipLaunchKernelGGL((b2b_ffn_kernel<N1, D>), grid, block, 0, st, p);

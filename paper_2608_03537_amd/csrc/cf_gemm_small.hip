@@ -54,28 +54,6 @@ struct Small {
   static_assert(32 * TM <= kRecPeers * kRecRows, "records of 32 peers");
 };
 
-// Four 16-byte LDS reads of every 32-row block b < NB (4 KB apart) at a[0..3],
-// and the wait for them (inline assembly: the compiler would wait for all
-// outstanding direct-to-LDS loads in front of them).
-__device__ __forceinline__ void read_blocks(u32x4_t (&f)[2][4], const uint32_t (&a)[4]) {
-  asm volatile(
-      "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
-      "ds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %9 offset:4096\n\t"
-      "ds_read_b128 %6, %10 offset:4096\n\tds_read_b128 %7, %11 offset:4096\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(f[0][0]), "=&v"(f[0][1]), "=&v"(f[0][2]), "=&v"(f[0][3]), "=&v"(f[1][0]), "=&v"(f[1][1]),
-        "=&v"(f[1][2]), "=&v"(f[1][3])
-      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
-      : "memory");
-}
-__device__ __forceinline__ void read_blocks(u32x4_t (&f)[1][4], const uint32_t (&a)[4]) {
-  asm volatile(
-      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
-      "s_waitcnt lgkmcnt(0)"
-      : "=&v"(f[0][0]), "=&v"(f[0][1]), "=&v"(f[0][2]), "=&v"(f[0][3])
-      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
-      : "memory");
-}
 // The K x N form: fragments of one 32-column block by transposing reads, k
 // rows of ROWB bytes; a0 and a1 address the k rows 0..3 and 4..7 of the lane's
 // first chunk (k step 0), the steps are 16 rows apart.
@@ -93,19 +71,6 @@ __device__ __forceinline__ void read_block_kn(u32x4_t (&w)[4], uint32_t a0, uint
       : "memory");
 #pragma unroll
   for (int ks = 0; ks < 4; ++ks) w[ks] = u32x4_t{v[2 * ks][0], v[2 * ks][1], v[2 * ks + 1][0], v[2 * ks + 1][1]};
-}
-
-template <int TPR>
-__device__ __forceinline__ float row_sum(float v) {
-#pragma unroll
-  for (int o = 1; o < TPR; o <<= 1) v += __shfl_xor(v, o);
-  return v;
-}
-template <int TPR>
-__device__ __forceinline__ float row_max(float v) {
-#pragma unroll
-  for (int o = 1; o < TPR; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
 }
 
 // Publishes (a, b) of the lane's row (b unless MAX) and reads the peers'

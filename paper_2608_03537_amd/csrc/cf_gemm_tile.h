@@ -268,6 +268,46 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 // ---------------------------------------------------------------------------
+// Helpers of the kernels whose waves keep operand rings of their own (small
+// GEMM tiles, few-row FFN).
+// ---------------------------------------------------------------------------
+// Four 16-byte LDS reads of every 32-row block b < NB (4 KB apart) at a[0..3],
+// and the wait for them (inline assembly: the compiler would wait for all
+// outstanding direct-to-LDS loads in front of them).
+__device__ __forceinline__ void read_blocks(u32x4_t (&f)[2][4], const uint32_t (&a)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+      "ds_read_b128 %4, %8 offset:4096\n\tds_read_b128 %5, %9 offset:4096\n\t"
+      "ds_read_b128 %6, %10 offset:4096\n\tds_read_b128 %7, %11 offset:4096\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(f[0][0]), "=&v"(f[0][1]), "=&v"(f[0][2]), "=&v"(f[0][3]), "=&v"(f[1][0]), "=&v"(f[1][1]),
+        "=&v"(f[1][2]), "=&v"(f[1][3])
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+      : "memory");
+}
+__device__ __forceinline__ void read_blocks(u32x4_t (&f)[1][4], const uint32_t (&a)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(f[0][0]), "=&v"(f[0][1]), "=&v"(f[0][2]), "=&v"(f[0][3])
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+      : "memory");
+}
+// Sum / maximum over TPR neighbouring lanes (a power of two).
+template <int TPR>
+__device__ __forceinline__ float row_sum(float v) {
+#pragma unroll
+  for (int o = 1; o < TPR; o <<= 1) v += __shfl_xor(v, o);
+  return v;
+}
+template <int TPR>
+__device__ __forceinline__ float row_max(float v) {
+#pragma unroll
+  for (int o = 1; o < TPR; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
+  return v;
+}
+
+// ---------------------------------------------------------------------------
 // Main loop v2: direct global -> LDS loads (global_load_lds_dwordx4), a ring
 // of S::STAGES stages, no register staging.  A stage holds 128 bytes of k for
 // the TN rows of W^T followed by the TM rows of X.  Needs K / V2_TK >= STAGES-1

@@ -112,6 +112,35 @@ def run_attn(Q, K, V, scale=None):
 # Ragged Lk puts the partial last key block in either ring stage: with an odd
 # block count (300, 289 keys) it is loaded from stage 1's step, with an even
 # one (333, 350) from stage 0's, for both head dimensions.
+@pytest.mark.parametrize("d,N1", [(64, 128), (128, 256), (256, 256), (256, 512)])
+@pytest.mark.parametrize("batch,M,own", [(1, 1, True), (1, 33, False), (2, 1000, True), (1, 8192, False),
+                                         (1, 8193, True), (3, 2753, False)])
+def test_ffn_forms(batch, M, own, d, N1):
+    """Both sides of the 32-row / 128-row choice (256 row blocks of 32), every compiled shape, with R = X and without
+    gamma and beta (own) or with another R and an affine LayerNorm, against fp64 on the GPU."""
+    g = torch.Generator(device="cuda").manual_seed(M + N1 + d)
+    rnd = lambda *sh, std=1.0: torch.randn(sh, generator=g, device="cuda") * std
+    X = rnd(batch, M, d).bfloat16()
+    W1, W2 = rnd(N1, d, std=d ** -0.5).bfloat16(), rnd(d, N1, std=N1 ** -0.5).bfloat16()
+    b1, b2 = rnd(N1, std=0.5), rnd(d, std=0.5)
+    R = X if own else rnd(batch, M, d).bfloat16()
+    gamma, beta = (None, None) if own else (1.0 + rnd(d, std=0.1), rnd(d, std=0.1))
+    Y = cf.b2b_ffn(X, W1, b1, W2, b2, R, gamma, beta)
+    torch.cuda.synchronize()
+    x = X.double().reshape(-1, d)
+    h = x @ W1.double().t().contiguous() + b1.double()
+    o = (0.5 * h * (1.0 + torch.erf(h / 2 ** 0.5))) @ W2.double().t().contiguous() + b2.double()
+    o = o + R.double().reshape(-1, d)
+    o = o - o.mean(1, keepdim=True)
+    o = o / torch.sqrt(o.square().mean(1, keepdim=True) + 1e-5)
+    if not own:
+        o = o * gamma.double() + beta.double()
+    err = Y.double().reshape(-1, d) - o
+    # the suite's bf16 bounds, the largest error scaled with the largest value (an ulp at 4 is 2^-6)
+    assert float(err.square().sum().sqrt() / o.square().sum().sqrt()) < 5e-3
+    assert float((err.abs() / o.abs().clamp(min=1.0)).max()) < 2e-2
+
+
 @pytest.mark.parametrize("B,H,Lq,Lk,d", [(1, 2, 200, 300, 64), (2, 1, 129, 64, 128), (1, 3, 64, 1, 128),
                                          (1, 1, 256, 333, 128), (1, 2, 130, 289, 128), (1, 1, 100, 350, 64)])
 def test_attention_small(B, H, Lq, Lk, d):
