@@ -53,6 +53,9 @@ extern "C" {
 
 #define CF_VERSION 1
 #define CF_WS_HEADER_BYTES 8916992  /* 4096 + 2 stages * 2 parities * 64 slots * 17 records * 128 rows * 16 */
+/* A workspace query that returns this size means an optional workspace: with it
+   the call runs as row clusters, without it (NULL) on whole rows. */
+#define CF_WS_OPTIONAL_BYTES 8917008  /* CF_WS_HEADER_BYTES + 16 */
 #define CF_B2B_WS_HEADER_BYTES 1048576  /* split-MLP arrival counters: 262144 words of 4 bytes */
 
 typedef enum {
@@ -94,8 +97,9 @@ typedef enum {
  * bias/gamma/beta are fp32 [N] or NULL (= 0 / 1 / 0), Y is M x N (out_dtype).
  * dtypes: in {F32, BF16} with out == in, or in = BF16 with out = F32.
  * Shape rules: N % 32 == 0, K % 16 == 0, 32 <= N <= 8192.
- * Workspace: cf_gemm_postnorm_workspace() bytes (0 on the whole-row path),
- * 16-byte aligned.  Every non-empty workspace begins with CF_WS_HEADER_BYTES
+ * Workspace: cf_gemm_postnorm_workspace() bytes (0 on the whole-row path;
+ * CF_WS_OPTIONAL_BYTES where path 0 takes row clusters with a workspace and
+ * whole rows without one), 16-byte aligned.  Every non-empty workspace begins with CF_WS_HEADER_BYTES
  * of library state (an error word, the round counters and the exchange
  * records of the row-cluster path): zero-fill that header once before first
  * use and do not modify it afterwards; every call leaves it valid for any

@@ -26,6 +26,7 @@ CF_LAYOUT_KN, CF_LAYOUT_NK = 0, 1
 CF_MID_GELU_BIAS, CF_MID_SOFTMAX, CF_MID_RELU_BIAS = 0, 1, 2
 CF_OUT_STORE, CF_OUT_BIAS_RESIDUAL_LN, CF_OUT_BIAS_RELU = 0, 1, 2
 PATH_AUTO, PATH_WHOLE_ROW, PATH_CLUSTER, PATH_SPLIT = 0, 1, 2, 3
+CF_WS_OPTIONAL_BYTES = 8917008     # a workspace query's answer where the workspace may be left out
 CF_B2B_WS_HEADER_BYTES = 1 << 20   # split-MLP arrival counters at the start of its workspace
 STATUS = {0: "CF_OK", 1: "CF_ERR_NULL", 2: "CF_ERR_SHAPE", 3: "CF_ERR_LD", 4: "CF_ERR_ALIGN",
           5: "CF_ERR_DTYPE", 6: "CF_ERR_WORKSPACE", 7: "CF_ERR_UNSUPPORTED", 8: "CF_ERR_ALIAS",
@@ -232,11 +233,24 @@ def check_workspace(ws, stream=None):
         _check(cf_workspace_check(_ptr(ws), ws.numel(), _stream(stream)))
 
 
+def _row_workspace(ws, need, device, stream, check):
+    """The workspace to pass for a row call whose query answered ``need``.  An
+    optional one is left out where using it would make the call synchronise
+    (``check``) or allocate while a graph is being captured."""
+    if need == CF_WS_OPTIONAL_BYTES:
+        if check:
+            return None
+        if ws is None and _capturing():
+            ws = _ws_cache.get((str(device), _stream(stream), "rows"))
+            return ws if ws is not None and ws.numel() >= need else None
+    return workspace(need, device, stream) if ws is None else ws
+
+
 def _after_call(ws, need, stream, check):
     # The error word exists only when the plan used a workspace; checking
     # synchronises, so it is skipped while a graph is being captured (the
     # caller then checks after replaying, with check_workspace).
-    if check and need > 0 and not _capturing():
+    if check and need > 0 and need != CF_WS_OPTIONAL_BYTES and not _capturing():
         check_workspace(ws, stream)
 
 
@@ -273,8 +287,7 @@ def gemm_postnorm(X, W, bias=None, R=None, gamma=None, beta=None, *, w_layout=CF
     Y = out if out is not None else torch.empty((M, N), dtype=out_dtype or X.dtype, device=X.device)
     a = postnorm_args(X, W, bias, R, gamma, beta, Y, w_layout=w_layout, alpha=alpha, eps=eps, path=path)
     need = cf_gemm_postnorm_workspace(a)
-    if ws is None:
-        ws = workspace(need, X.device, stream)
+    ws = _row_workspace(ws, need, X.device, stream, check)
     _check(cf_gemm_postnorm(a, _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
     _after_call(ws, need, stream, check)
     return Y
@@ -315,8 +328,7 @@ def gemm_subgraph(X, W, spec, *, w_layout=CF_LAYOUT_NK, path=PATH_AUTO, ws=None,
     nodes = make_nodes(spec)
     a = subgraph_args(X, W, nodes, w_layout=w_layout, path=path)
     need = cf_gemm_subgraph_workspace(a)
-    if ws is None:
-        ws = workspace(need, X.device, stream)
+    ws = _row_workspace(ws, need, X.device, stream, check)
     _check(cf_gemm_subgraph(a, _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
     _after_call(ws, need, stream, check)
 

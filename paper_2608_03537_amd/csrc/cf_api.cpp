@@ -89,6 +89,7 @@ struct Plan {
   int kidx = -1, mode = ROWS_LOCAL, cn = 1, num_rb = 0, slots = 0, tm = 0, tn = 0;
   size_t ws = 0;
   size_t off_part = 0, off_x = 0;
+  bool optional = false;   // the workspace may be left out: the plan is then whole rows
 };
 
 constexpr int kAssumedCUs = 256;   // MI355X; used only to rank tile widths
@@ -179,10 +180,26 @@ double plan_cost(const GemmKernel& t, int64_t rounds, int64_t wgs, int64_t K, bo
   // several rounds of small tiles were measured up to 15 % over the estimate
   return t.epi == 3 && rounds > 1 ? 1.15 * c : c;
 }
+// Rounds of row blocks of cn peers: the groups resident on the 8 XCDs of 32 CUs.
+int64_t cluster_rounds(int64_t rb, int64_t cn) {
+  const int64_t groups = 8 * std::max<int64_t>(1, std::min<int64_t>(kMaxSlots / 8, kAssumedCUs / 8 / cn));
+  return (rb + groups - 1) / groups;
+}
+// The same for whole rows (32 x TN tiles, one workgroup each): the tile's
+// operand stream (75 GB/s a CU) or its fp32 MFMAs.  Measured against 32 x 32 row
+// clusters: 128 x 256 x 256 7.3 / 6.6 us, fp32 15.2 / 7.9; 512 rows 7.7 / 7.1, fp32 15.6 / 8.4.
+double cost_whole(const GemmKernel& t, int64_t M, int64_t K) {
+  const int64_t wgs = (M + 31) / 32;
+  double step = (32.0 + t.tn) * (t.in_f32 ? 256 : 128) / 75e3;
+  if (t.in_f32) step = std::max(step, 2.0 * 32 * t.tn * 64 / 0.6e6);
+  if (t.loop == 0) step *= t.in_f32 ? 2.5 : 3.5;   // the register-staged loop: 512 x 320 x 784 35 us, fp32 97
+  return (double)((wgs + kAssumedCUs - 1) / kAssumedCUs) * (step * (double)((K + 63) / 64) + (t.in_f32 ? 3.0 : 0.8));
+}
 double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch, bool cluster) {
   const GemmKernel& t = gemm_kernel(idx);
-  const int64_t wgs = (M + t.tm - 1) / t.tm * ((N + t.tn - 1) / t.tn) * batch;
-  return plan_cost(t, (wgs + kAssumedCUs - 1) / kAssumedCUs, wgs, K, cluster);
+  const int64_t rb = (M + t.tm - 1) / t.tm, cn = (N + t.tn - 1) / t.tn, wgs = rb * cn * batch;
+  const int64_t rounds = cluster ? cluster_rounds(rb, cn) : (wgs + kAssumedCUs - 1) / kAssumedCUs;
+  return plan_cost(t, rounds, wgs, K, cluster);
 }
 
 // The kernel of least cost among the small tiles (32 x 32, 32 x 64, 64 x 64) and,
@@ -211,8 +228,7 @@ int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop,
     int64_t rounds = (wgs + kAssumedCUs - 1) / kAssumedCUs;
     if (cluster) {
       if (N % t.tn != 0 || cn > t.peers || kArriveUnit % (unsigned long long)cn != 0) continue;
-      const int64_t groups = 8 * std::min<int64_t>(kMaxSlots / 8, kAssumedCUs / 8 / cn);
-      rounds = (rb + groups - 1) / groups;
+      rounds = cluster_rounds(rb, cn);
     }
     const double c = plan_cost(gemm_kernel(idx), rounds, wgs, K, cluster);
     if (c < limit) { limit = c; best = idx; }
@@ -225,7 +241,7 @@ int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop,
 // true when the subgraph has a row reduction (then rows must be completed
 // across tiles); without one any tiling is valid.
 cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int path, int epi, bool need_rows,
-                    bool probe_device, Plan& pl, bool allow_cluster = true, int64_t batch = 1) {
+                    Plan& pl, bool allow_cluster = true, int64_t batch = 1, bool use_optional = true) {
   pl = Plan();
   if (!allow_cluster && need_rows) {
     if (path == PATH_CLUSTER)
@@ -298,7 +314,20 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     // as a row cluster or (row pass and second launch: about 4 us) small ones as
     // the plain product of the split path.  Only where the automatic choice already
     // takes a workspace, and not under an explicit path.
-    if (automatic && pl.kidx >= 0 && pl.mode != ROWS_LOCAL) {
+    if (automatic && pl.kidx >= 0 && pl.mode == ROWS_LOCAL && use_optional) {
+      // Whole rows of 32 x TN on few CUs, or wide ones in many rounds: row
+      // clusters if the caller gives a workspace and they are clearly faster.
+      const double now = 0.85 * cost_whole(gemm_kernel(pl.kidx), M, K);
+      const int ck = tile_128(1, true, kAutoClusterPeers);
+      const double c128 = ck >= 0 ? cost_128(ck, M, N, K, 1, true) : now;
+      int sc = pick_small(M, N, K, in_f32, w_nk, loop, 1, true, std::min(now, c128));
+      if (sc < 0 && c128 < now) sc = ck;
+      if (sc >= 0) {
+        pl.kidx = sc;
+        pl.mode = ROWS_CLUSTER;
+        pl.optional = true;
+      }
+    } else if (automatic && pl.kidx >= 0 && pl.mode != ROWS_LOCAL) {
       const double now = cost_128(pl.kidx, M, N, K, 1, pl.mode == ROWS_CLUSTER);
       const int sc = !allow_cluster ? -1 : pick_small(M, N, K, in_f32, w_nk, loop, 1, true,
                                                       pl.mode == ROWS_SPLIT ? now + 4.0 : now);
@@ -320,13 +349,6 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
   pl.cn = (int)((N + t.tn - 1) / t.tn);
   pl.num_rb = (int)((M + t.tm - 1) / t.tm);
   pl.slots = (pl.num_rb + 7) / 8;
-  if (pl.mode == ROWS_CLUSTER && probe_device) {
-    // Every peer group must be resident at once: cap the persistent grid.
-    const int cap = resident_wgs(pl.kidx);
-    const int slots = cap / (8 * pl.cn);
-    if (slots < 1) return fail(CF_ERR_UNSUPPORTED, "cluster path: %d peers do not fit the device", pl.cn);
-    pl.slots = std::min(pl.slots, std::min(slots, kMaxSlots / 8));
-  }
   // the finish pass reads a row's partials one per lane of a 64-lane wave
   if (pl.mode == ROWS_SPLIT && t.epi == 2 && pl.cn > 64)
     return fail(CF_ERR_UNSUPPORTED, "split path: %d tiles per row exceed 64", pl.cn);
@@ -334,6 +356,16 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     return fail(CF_ERR_UNSUPPORTED, "cluster path: tile of %d rows x %d peers exceeds the exchange records",
                 pl.tm, pl.cn);
   size_workspace(pl, M, N, allow_cluster);
+  return CF_OK;
+}
+
+// Row clusters: every peer group must be resident at once, so the persistent
+// grid is capped (queries the device, hence only right before a launch).
+cf_status cap_slots(Plan& pl) {
+  if (pl.mode != ROWS_CLUSTER) return CF_OK;
+  const int slots = resident_wgs(pl.kidx) / (8 * pl.cn);
+  if (slots < 1) return fail(CF_ERR_UNSUPPORTED, "cluster path: %d peers do not fit the device", pl.cn);
+  pl.slots = std::min(pl.slots, std::min(slots, kMaxSlots / 8));
   return CF_OK;
 }
 
@@ -548,13 +580,17 @@ cf_status rows_common(int64_t M, int64_t N, int64_t K, cf_dtype in, const void* 
   Plan pl;
   // Validation and sizing never touch the device; residency is queried only
   // right before a launch.
-  if ((s = plan_rows(M, N, K, in == CF_F32, wl == CF_LAYOUT_NK, path, epi_kind, need_rows, false, pl,
-                     !scratch)) != CF_OK)
+  if ((s = plan_rows(M, N, K, in == CF_F32, wl == CF_LAYOUT_NK, path, epi_kind, need_rows, pl, !scratch)) != CF_OK)
     return s;
   if (size_only) {
-    *ws_out = pl.ws;
+    *ws_out = pl.ws + (pl.optional ? CF_WS_OPTIONAL_BYTES - CF_WS_HEADER_BYTES : 0);
     return CF_OK;
   }
+  const bool use_optional = ws && ws_bytes >= pl.ws && aligned16(ws);
+  if (pl.optional && !use_optional &&
+      (s = plan_rows(M, N, K, in == CF_F32, wl == CF_LAYOUT_NK, path, epi_kind, need_rows, pl, !scratch, 1,
+                     false)) != CF_OK)
+    return s;
   for (const void* out : {(const void*)epi.Y, (const void*)epi.s_out, (const void*)epi.q_out})
     if (outputs_alias(out, {X, W, epi.R, (const void*)epi.bias, (const void*)epi.gamma, (const void*)epi.beta}))
       return fail(CF_ERR_ALIAS, "an output aliases an input");
@@ -568,9 +604,7 @@ cf_status rows_common(int64_t M, int64_t N, int64_t K, cf_dtype in, const void* 
     if (!aligned16(ws)) return fail(CF_ERR_ALIGN, "workspace is not 16-byte aligned");
   }
   if (M == 0) return CF_OK;
-  if (pl.mode == ROWS_CLUSTER &&
-      (s = plan_rows(M, N, K, in == CF_F32, wl == CF_LAYOUT_NK, path, epi_kind, need_rows, true, pl)) != CF_OK)
-    return s;
+  if ((s = cap_slots(pl)) != CF_OK) return s;
   GemmRowsParams p{};
   p.batch = 1;
   p.M = (int)M;
@@ -755,8 +789,8 @@ cf_status cf_gemm(int64_t batch, int64_t M, int64_t N, int64_t K, cf_dtype in, c
     if (outputs_alias(C, {A, B, (const void*)bias})) return fail(CF_ERR_ALIAS, "C aliases an input");
     if (M == 0 || batch == 0) return CF_OK;
     Plan pl;
-    if ((s = plan_rows(M, N, K, in == CF_F32, b_layout == CF_LAYOUT_NK, PATH_AUTO, 0, false, false, pl, true,
-                       batch)) != CF_OK)
+    if ((s = plan_rows(M, N, K, in == CF_F32, b_layout == CF_LAYOUT_NK, PATH_AUTO, 0, false, pl, true, batch)) !=
+        CF_OK)
       return s;
     GemmRowsParams p{};
     p.batch = (int)batch;

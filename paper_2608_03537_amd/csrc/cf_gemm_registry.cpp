@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <mutex>
 #include <vector>
 
@@ -9,26 +10,44 @@
 
 namespace cf {
 
-static std::vector<GemmKernel>& table() {
-  static std::vector<GemmKernel> t;
-  static std::once_flag once;
-  std::call_once(once, [] {
+// Every compiled kernel, and its index by (fp32 input, tile rows, tile columns,
+// main loop, epilogue): planning a call looks up about twenty candidates, which
+// a search of the table made a noticeable part of a short call's host time.
+namespace {
+struct Registry {
+  std::vector<GemmKernel> all;
+  std::array<int16_t, 2 * 4 * 8 * 3 * 4> index;
+  static int key(int in_f32, int tm, int tn, int loop, int epi) {
+    const int r = tm == 32 ? 0 : tm == 64 ? 1 : tm == 128 ? 2 : tm == 256 ? 3 : -1;
+    const int c = tn == 32 ? 0 : tn == 64 ? 1 : tn == 128 ? 2 : tn == 192 ? 3 : tn == 256 ? 4 : tn == 384 ? 5
+                  : tn == 512 ? 6 : tn == 768 ? 7 : -1;
+    if (r < 0 || c < 0 || loop < 0 || loop > 2 || epi < 0 || epi > 3) return -1;
+    return ((((in_f32 != 0) * 4 + r) * 8 + c) * 3 + loop) * 4 + epi;
+  }
+  Registry() {
+    index.fill(-1);
     for (auto get : {gemm_kernels_v2, gemm_kernels_v1, gemm_kernels_wr, gemm_kernels_split, gemm_kernels_kn,
                      gemm_kernels_big, gemm_kernels_small}) {
       int n = 0;
       const GemmKernel* k = get(&n);
-      t.insert(t.end(), k, k + n);
+      all.insert(all.end(), k, k + n);
     }
-  });
-  return t;
+    for (size_t i = 0; i < all.size(); ++i) {
+      const int q = key(all[i].in_f32, all[i].tm, all[i].tn, all[i].loop, all[i].epi);
+      if (q >= 0 && index[q] < 0) index[q] = (int16_t)i;
+    }
+  }
+};
+const Registry& registry() {
+  static const Registry r;
+  return r;
 }
+const std::vector<GemmKernel>& table() { return registry().all; }
+}  // namespace
 
 int find_gemm_kernel(int in_f32, int tm, int tn, int loop, int epi) {
-  const auto& t = table();
-  for (size_t i = 0; i < t.size(); ++i)
-    if (t[i].in_f32 == in_f32 && t[i].tm == tm && t[i].tn == tn && t[i].loop == loop && t[i].epi == epi)
-      return (int)i;
-  return -1;
+  const int q = Registry::key(in_f32, tm, tn, loop, epi);
+  return q < 0 ? -1 : registry().index[q];
 }
 
 const GemmKernel& gemm_kernel(int idx) { return table()[idx]; }

@@ -130,3 +130,32 @@ def test_peer_wait_failure_is_reported():
     torch.cuda.synchronize()
     ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, inp.gamma, inp.beta, 1.0, inp.eps)
     assert_close_bf16(host(Y), ref, "after a reported failure")
+
+
+@pytest.mark.parametrize("dtype,M,K,N", [("f32", 128, 256, 256), ("bf16", 200, 400, 224), ("f32", 70, 272, 320),
+                                         ("bf16", 9000, 768, 768)])
+def test_optional_workspace(dtype, M, K, N):
+    """Shapes whose workspace is optional: whole rows without one (or with one too small), row clusters with it; the
+    helper leaves it out unless check=False."""
+    inp = I.postnorm_inputs(M, K, N, dtype, seed=55, bias_std=0.5, gamma="uniform", beta_std=0.3)
+    X, W, R = (dev(t, dtype) for t in (inp.X, I.lay_out_weight(inp.W, "nk"), inp.R))
+    b, g, be = (dev(t, "f32") for t in (inp.bias, inp.gamma, inp.beta))
+    check = assert_close_f32 if dtype == "f32" else assert_close_bf16
+    ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, inp.gamma, inp.beta, 1.0, inp.eps)
+    a = cf.postnorm_args(X, W, b, R, g, be, torch.empty_like(R), eps=inp.eps)
+    assert cf.cf_gemm_postnorm_workspace(a) == cf.CF_WS_OPTIONAL_BYTES
+    ws = torch.zeros(cf.CF_WS_OPTIONAL_BYTES, dtype=torch.uint8, device="cuda")
+    for p, n in ((None, 0), (ws.data_ptr(), 4096), (ws.data_ptr() + 8, ws.numel() - 8)):
+        Y = torch.empty_like(R)
+        a.Y = Y.data_ptr()
+        cf._check(cf.cf_gemm_postnorm(a, p, n, torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        assert int(ws.sum()) == 0                      # not touched
+        check(host(Y), ref, "whole rows")
+    whole = cf.gemm_postnorm(X, W, b, R, g, be, eps=inp.eps, ws=ws)
+    assert int(ws.sum()) == 0 and torch.equal(whole, Y)
+    for _ in range(2):
+        Y = cf.gemm_postnorm(X, W, b, R, g, be, eps=inp.eps, ws=ws, check=False)
+        cf.check_workspace(ws)
+        check(host(Y), ref, "row clusters")
+    assert int(ws.sum()) != 0
