@@ -445,6 +445,311 @@ void b2b_mlp_whole_kernel(B2BParams p) {
   }
 }
 
+// Wide form of the whole-row-block kernel, for N1 = 512: all hidden units at
+// once.  The chunked form above streams X once per 256 units, and its 128 x 256
+// product is bound by the CU's load path (48 KB a 64-deep k step at about 32 bytes
+// a clock, 0.96 us a step however the waves are arranged); 128 x 512 streams 80 KB
+// for twice the products, about 1.3 us a step.  (With more hidden units O would
+// have to stay in registers through the next 512: 64 spilled registers, 137 us
+// against the chunked form's 108 at 65536 x 512 x 1024.)
+//
+// ML1 (128 rows x 512 hidden units) runs on eight waves in two groups one section
+// apart, as the 256 x 256 GEMM tile: a wave alternates a read section (LDS
+// fragments) with an MFMA section (8 MFMAs, the loads between them), and waves w
+// and w + 4, which share a SIMD, are in opposite sections.  A k step has five 16 KB
+// pieces: X (128 rows) and W0..W3 (128 hidden rows each); wave (wm, wn) owns rows
+// 64 wm .. +63 and hidden units 32 wn .. +31 of every W piece.  Phase i multiplies X by
+// Wi; the read sections of phases 0..3 read X; W1; W2; W3 and the next step's W0.
+// LDS holds nine pieces in a ring, in the order W0 X W1 W2 W3 of each step: a
+// piece's space takes the ninth piece after it one phase after its read, about
+// six phases before that piece is read.  The four quarters of the first half of
+// the W2^T chunk follow the last step through the ring as pieces of a further step.
+//
+// Waits (two loads a piece and wave, issued in ring order): at the end of the
+// read section of phase 0 the pieces younger than W1(k) are W2(k) W3(k) W0(k+1) X(k+1)
+// W1(k+1); phase 1, younger than W2(k): W3(k) .. W1(k+1) W2(k+1) W3(k+1); phase 2, younger
+// than W0(k+1): X(k+1) .. W0(k+2); phase 3, younger than X(k+1): W1(k+1) .. X(k+2).
+//
+// ML2: wave (wm, wn) takes rows 64 wm .. +63 and output columns 32 wn .. +31, over the
+// two halves of the 512 hidden units in turn; S = ReLU(P + b1) goes through LDS in
+// fragment order.  Each output element has one owner.
+namespace {
+constexpr int kWPiece = 16384, kWSlots = 9;
+
+// Fragments of two 32-row blocks (4 KB apart), of one, and of two at different places.
+__device__ __forceinline__ void read_one(u32x4_t (&w)[4], const uint32_t (&a)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+      : "memory");
+}
+__device__ __forceinline__ void read_two(u32x4_t (&u)[4], u32x4_t (&w)[4], const uint32_t (&a)[4],
+                                         const uint32_t (&b)[4]) {
+  asm volatile(
+      "ds_read_b128 %0, %8\n\tds_read_b128 %1, %9\n\tds_read_b128 %2, %10\n\tds_read_b128 %3, %11\n\t"
+      "ds_read_b128 %4, %12\n\tds_read_b128 %5, %13\n\tds_read_b128 %6, %14\n\tds_read_b128 %7, %15\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(u[0]), "=&v"(u[1]), "=&v"(u[2]), "=&v"(u[3]), "=&v"(w[0]), "=&v"(w[1]), "=&v"(w[2]), "=&v"(w[3])
+      : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(b[0]), "v"(b[1]), "v"(b[2]), "v"(b[3])
+      : "memory");
+}
+}  // namespace
+
+template <int N2>
+__global__ __launch_bounds__(512, 1) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void b2b_mlp_wide_kernel(B2BParams p) {
+  static_assert(N2 == 128, "four wave columns of 32 outputs");
+  constexpr int W2_ROWB = kMlpHidden * 2;           // bytes of one row of a W2^T half (256 hidden units)
+  constexpr int PT_ROWB = N2 * 4 + 16;              // staged fp32 output row
+  constexpr int LDS = kWSlots * kWPiece;
+  static_assert(kMlpRows * PT_ROWB <= LDS && N2 * W2_ROWB == 4 * kWPiece, "LDS budget");
+  __shared__ __attribute__((aligned(16))) char smem[LDS];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 2, wn = wave & 3;          // waves 0..3: wm 0, waves 4..7: wm 1
+  const int lr = lane & 31, lg = lane >> 5;
+  const int m0 = blockIdx.x * kMlpRows, bz = blockIdx.y;
+  const char* X = reinterpret_cast<const char*>(p.X + (int64_t)bz * p.sx + (int64_t)m0 * p.ldx);
+  const char* W1 = reinterpret_cast<const char*>(p.W1 + (int64_t)bz * p.sw1);
+  const char* W2 = reinterpret_cast<const char*>(p.W2 + (int64_t)bz * p.sw2);
+  const int KT = p.K / 64;
+
+  // Load j (of two) of this wave for an X or W piece: rows 8 (2 wave + j) .. +7 of
+  // 128 bytes, the 16-byte chunk ch of row r at position ch ^ ((r >> 1) & 7)
+  // (conflict-free fragment reads).  The W1^T rows of every 32-row block are
+  // taken in perm23 order.  A W2^T quarter holds 32 output rows of 512 bytes, chunk
+  // q of row r at position q ^ (r & 15); a load fills two rows.
+  uint32_t xo[2], wo[2], vo[2];
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int ld = 2 * wave + j, row = 8 * ld + (lane >> 3), ch = (lane & 7) ^ ((row >> 1) & 7);
+    xo[j] = (uint32_t)(min(row, p.M - 1 - m0) * (int)p.ldx * 2 + ch * 16);
+    wo[j] = (uint32_t)(((row & ~31) | perm23(row & 31)) * (int)p.ldw1 * 2 + ch * 16);
+    const int r = 2 * ld + (lane >> 5);
+    vo[j] = (uint32_t)(r * (int)p.ldw2 * 2 + ((lane & 31) ^ (r & 15)) * 16);
+  }
+  // Ring position of piece i of step st (0 W0, 1 X, 2..4 W1..W3), rotated so that
+  // the pieces of step KT start at slot 0.
+  const int rot = (kWSlots - 5 * KT % kWSlots) % kWSlots;
+  auto at = [&](int st, int i) { return (5 * st + i + rot) % kWSlots * kWPiece; };
+  const uint32_t s0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)smem);
+  uint32_t xa[4], wa[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+    const int ch = ((2 * ks + lg) ^ ((lr >> 1) & 7)) << 4;
+    xa[ks] = s0 + (wm * 64 + lr) * 128 + ch;
+    wa[ks] = s0 + (wn * 32 + lr) * 128 + ch;
+  }
+  const int64_t wpiece = (int64_t)128 * p.ldw1 * 2, vq = (int64_t)32 * p.ldw2 * 2;
+
+  // P + b1: the accumulators start from b1 (element 4 g + q of lane half lg holds
+  // hidden unit 16 (g / 2) + 8 lg + 4 (g % 2) + q of the wave's 32)
+  f32x16_t acc[2][4];   // [32-row block][W piece]
+#pragma unroll
+  for (int h = 0; h < 4; ++h)
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      const int n = h * 128 + wn * 32 + 16 * (g >> 1) + 8 * lg + 4 * (g & 1);
+      const f32x4_t b = p.b1 ? *reinterpret_cast<const f32x4_t*>(p.b1 + n) : f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[0][h][4 * g + q] = acc[1][h][4 * g + q] = b[q];
+    }
+  __builtin_amdgcn_sched_barrier(0);
+  auto load_x = [&](int st, int j) {
+    dma16(X + (int64_t)st * 128 + xo[j], smem + at(st, 1) + (2 * wave + j) * 1024);
+  };
+  auto load_w = [&](int st, int h, int j) {
+    dma16(W1 + h * wpiece + (int64_t)st * 128 + wo[j], smem + at(st, h == 0 ? 0 : h + 1) + (2 * wave + j) * 1024);
+  };
+  // Quarter q of the W2^T half at hidden offset `off` (bytes) into slot q.
+  auto load_v = [&](int off, int q, int j) {
+    dma16(W2 + off + q * vq + vo[j], smem + q * kWPiece + (2 * wave + j) * 1024);
+  };
+  u32x4_t xf[2][4], w[2][4];
+  auto mma = [&](auto piece_t, auto&& load) {
+    constexpr int H = decltype(piece_t)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_setprio(1);
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks)
+#pragma unroll
+      for (int bm = 0; bm < 2; ++bm) {
+        Mma<bf16_t>::run(acc[bm][H], w[H & 1][ks], xf[bm][ks]);
+        if (bm == 1) {
+          __builtin_amdgcn_sched_barrier(0);
+          load(ks);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+    lds_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  using P0 = std::integral_constant<int, 0>;
+  using P1 = std::integral_constant<int, 1>;
+  using P2 = std::integral_constant<int, 2>;
+  using P3 = std::integral_constant<int, 3>;
+  // Step k, LEFT steps after it (2: at least two).
+  auto step = [&](int k, auto left_t) {
+    constexpr int LEFT = decltype(left_t)::value;
+    uint32_t a[4], b[4];
+    auto addr = [&](uint32_t (&d)[4], const uint32_t (&base)[4], int off) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) d[ks] = base[ks] + (uint32_t)off;
+    };
+    addr(a, xa, at(k, 1));
+    read_blocks(xf, a);
+    wait_vmcnt<10>();
+    lds_barrier();
+    mma(P0{}, [&](int i) {
+      if (LEFT >= 1) load_w(k + 1, i < 2 ? 2 : 3, i & 1);
+      else if (i < 2) load_v(0, 3, i);
+    });
+    addr(a, wa, at(k, 2));
+    read_one(w[1], a);
+    wait_vmcnt<(LEFT >= 1 ? 12 : 10)>();
+    lds_barrier();
+    mma(P1{}, [&](int i) {
+      if (i >= 2) return;
+      if (LEFT >= 2) load_w(k + 2, 0, i);
+      else if (LEFT == 1) load_v(0, 0, i);
+    });
+    addr(a, wa, at(k, 3));
+    read_one(w[0], a);
+    wait_vmcnt<(LEFT >= 1 ? 10 : 8)>();
+    lds_barrier();
+    mma(P2{}, [&](int i) {
+      if (i >= 2) return;
+      if (LEFT >= 2) load_x(k + 2, i);
+      else if (LEFT == 1) load_v(0, 1, i);
+    });
+    addr(a, wa, at(k, 4));
+    if constexpr (LEFT >= 1) {
+      addr(b, wa, at(k + 1, 0));
+      read_two(w[1], w[0], a, b);
+      wait_vmcnt<10>();
+    } else {
+      read_one(w[1], a);
+    }
+    lds_barrier();
+    mma(P3{}, [&](int i) {
+      if (i >= 2) return;
+      if (LEFT >= 2) load_w(k + 2, 1, i);
+      else if (LEFT == 1) load_v(0, 2, i);
+    });
+  };
+  // The first eight pieces, in ring order.
+#pragma unroll
+  for (int j = 0; j < 2; ++j) load_w(0, 0, j);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) load_x(0, j);
+#pragma unroll
+  for (int h = 1; h < 4; ++h)
+#pragma unroll
+    for (int j = 0; j < 2; ++j) load_w(0, h, j);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) load_w(1, 0, j);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) load_x(1, j);
+#pragma unroll
+  for (int j = 0; j < 2; ++j) load_w(1, 1, j);
+  wait_vmcnt<14>();
+  lds_barrier();
+  {
+    const uint32_t a[4] = {wa[0] + (uint32_t)at(0, 0), wa[1] + (uint32_t)at(0, 0), wa[2] + (uint32_t)at(0, 0),
+                           wa[3] + (uint32_t)at(0, 0)};
+    read_one(w[0], a);
+  }
+  wait_vmcnt<12>();
+  lds_barrier();
+  if (wave >= 4) lds_barrier();   // one section behind
+  int k = 0;
+  for (; k < KT - 2; ++k) step(k, std::integral_constant<int, 2>{});
+  step(k, std::integral_constant<int, 1>{});
+  step(k + 1, std::integral_constant<int, 0>{});
+  if (wave < 4) lds_barrier();
+  wait_vmcnt<0>();                // the W2^T quarters
+  __syncthreads();
+
+  // ML2 over half hf of the hidden units: S = ReLU(P + b1) as bf16 fragments in
+  // slots 4..7, [wm][32-row block][k step of 16 hidden units][lane][16 B]; W2^T rows
+  // 32 wn .. +31 are quarter wn.
+  f32x16_t o[2];
+#pragma unroll
+  for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) o[bm][i] = 0.0f;
+  char* const xs = smem + (4 + 2 * wm) * kWPiece + lane * 16;
+  const char* const w2l = smem + wn * kWPiece + lr * W2_ROWB;
+#pragma unroll
+  for (int hf = 0; hf < 2; ++hf) {
+    if (hf == 1) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) load_v(512, q, j);
+    }
+#pragma unroll
+    for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+          const f32x16_t& v = acc[bm][2 * hf + h];
+          u32x4_t f;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            f[e] = pack_bf16x2(fmaxf(v[8 * s + 2 * e], 0.0f), fmaxf(v[8 * s + 2 * e + 1], 0.0f));
+          lds_write16(xs + (bm * 16 + h * 8 + wn * 2 + s) * 1024, f);
+        }
+    wait_vmcnt<0>();
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < 16; ++ks) {
+      const u32x4_t a = lds_read16(w2l + (((2 * ks + lg) ^ (lr & 15)) << 4));
+#pragma unroll
+      for (int bm = 0; bm < 2; ++bm) Mma<bf16_t>::run(o[bm], a, lds_read16(xs + (bm * 16 + ks) * 1024));
+    }
+    __syncthreads();   // every wave is done with the W2^T half and the S exchange
+  }
+
+  // O to LDS (fp32 rows), then + b2 (ReLU) as bf16: thread t takes 8 columns of
+  // row t / 16 + 32 j, so every wave-wide store covers four whole rows.
+#pragma unroll
+  for (int bm = 0; bm < 2; ++bm)
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      *reinterpret_cast<f32x4_t*>(smem + (wm * 64 + bm * 32 + lr) * PT_ROWB + (wn * 32 + 8 * g + 4 * lg) * 4) =
+          f32x4_t{o[bm][4 * g], o[bm][4 * g + 1], o[bm][4 * g + 2], o[bm][4 * g + 3]};
+  const int n = (tid & 15) * 8;
+  uint16_t* O = p.O + (int64_t)bz * p.so;
+  float bb[8] = {};
+  if (p.b2) {
+    load4<float>(p.b2 + n, reinterpret_cast<float(&)[4]>(bb[0]));
+    load4<float>(p.b2 + n + 4, reinterpret_cast<float(&)[4]>(bb[4]));
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int r = (tid >> 4) + 32 * j, m = m0 + r;
+    if (m >= p.M) continue;
+    const float* src = reinterpret_cast<const float*>(smem + r * PT_ROWB) + n;
+    float y[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      y[q] = src[q];
+      if (p.b2) y[q] += bb[q];
+      if (p.out_relu) y[q] = fmaxf(y[q], 0.0f);
+    }
+    const u32x4_t v = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3]), pack_bf16x2(y[4], y[5]),
+                       pack_bf16x2(y[6], y[7])};
+    __builtin_nontemporal_store(v, reinterpret_cast<u32x4_t*>(O + (int64_t)m * p.ldo + n));
+  }
+}
+
 bool b2b_mlp_supported(int K, int N1, int N2) {
   return N2 == 128 && N1 % kMlpHidden == 0 && N1 > 0 && K % 64 == 0 && K / 64 >= MlpS::STAGES - 1;
 }
@@ -452,8 +757,16 @@ bool b2b_mlp_supported(int K, int N1, int N2) {
 hipError_t launch_b2b_mlp(const B2BParams& p, hipStream_t st) {
   if (!b2b_mlp_supported(p.K, p.N1, p.N2) || (p.cn != 1 && p.cn != p.N1 / kMlpHidden)) return hipErrorInvalidValue;
   const unsigned rbs = (unsigned)((p.M + kMlpRows - 1) / kMlpRows);
-  const dim3 grid(rbs * (unsigned)p.cn, (unsigned)p.batch), block(MlpS::NT);
-  if (p.cn == 1) hipLaunchKernelGGL((b2b_mlp_whole_kernel<128>), grid, block, 0, st, p);
+  // N1 = 512: the wide form for every whole row block, and also where the chunks
+  // would be split but K is short: a workgroup then has little to stream, and the
+  // split form's commit costs more than the idle CUs.  Measured at N1 = 512 (us,
+  // wide / split): 4000 x 256 14.5 / 16.5, 16384 x 512 19.8 / 23.0, 4000 x 512 19.2 / 19.1,
+  // 16384 x 1024 29.3 / 29.7, 4000 x 1024 28.5 / 24.3; against the chunked whole form:
+  // 65536 x 1024 77.8 / 92 on one box (90.6 / 101 on another), 65536 x 256 33.7 / 45.7.
+  const bool wide = p.N1 == 512 && (p.cn == 1 || p.K <= 512);
+  const dim3 grid(rbs * (unsigned)(wide ? 1 : p.cn), (unsigned)p.batch), block(MlpS::NT);
+  if (wide) hipLaunchKernelGGL((b2b_mlp_wide_kernel<128>), grid, dim3(512), 0, st, p);
+  else if (p.cn == 1) hipLaunchKernelGGL((b2b_mlp_whole_kernel<128>), grid, block, 0, st, p);
   else hipLaunchKernelGGL((b2b_mlp_kernel<128>), grid, block, 0, st, p);
   return hipGetLastError();
 }

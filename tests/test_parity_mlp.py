@@ -164,3 +164,24 @@ def test_mlp_batched(shared_w1, shared_w2):
         ref = O.mlp_b2b(ins[b].X, w1[b], ins[0].b1, w2[b], ins[0].b2, out_relu=True)
         assert_close_bf16(got[b], ref, f"MLP batch entry {b}")
 
+
+
+@pytest.mark.parametrize("out_relu", [False, True])
+@pytest.mark.parametrize("batch,M,K", [(1, 32769, 128), (1, 32897, 192), (1, 33000, 1024), (3, 300, 320), (1, 1, 512)])
+def test_mlp_wide_form(batch, M, K, out_relu):
+    """N1 = 512 in one pass (128 x 512 products): two, three, five, eight and sixteen k steps (the ring of nine pieces
+    starts at different places), one row past a row block, batches; every element against fp64 on the GPU."""
+    g = torch.Generator(device="cuda").manual_seed(M + K)
+    rnd = lambda *sh, std=1.0: torch.randn(sh, generator=g, device="cuda") * std
+    X = rnd(batch, M, K).bfloat16()
+    W1, W2 = rnd(512, K, std=K ** -0.5).bfloat16(), rnd(128, 512, std=512 ** -0.5).bfloat16()
+    b1, b2 = rnd(512, std=0.5), rnd(128, std=0.5)
+    Y = cf.b2b_mlp(X, W1, b1, W2, b2, out_relu=out_relu)
+    torch.cuda.synchronize()
+    s = torch.relu(X.double().reshape(-1, K) @ W1.double().t().contiguous() + b1.double())
+    o = s @ W2.double().t().contiguous() + b2.double()
+    o = torch.relu(o) if out_relu else o
+    err = Y.double().reshape(-1, 128) - o
+    # the suite's bf16 bounds, the largest error scaled with the largest value (an ulp at 4 is 2^-6)
+    assert float(err.square().sum().sqrt() / o.square().sum().sqrt()) < 5e-3
+    assert float((err.abs() / o.abs().clamp(min=1.0)).max()) < 2e-2
