@@ -55,6 +55,95 @@ struct MlpLayout {
   static_assert(W2_LOADS % MlpS::NW == 0, "W2 loads per wave");
 };
 
+// Commit of a TM x N2 row-major tile held as column quads: thread t holds the
+// quad (t + NT j) % QPR of row (t + NT j) / QPR, so every wave-wide access
+// covers whole rows.  cn workgroups (c of them) share the rows; the partials
+// go through memory with device-coherent 16-byte accesses (sc1): the
+// workgroups of a row block need not share an XCD, and the reader reads only
+// after the writer's stores completed (arrival count).
+template <int TM, int NT, int N2>
+__device__ __forceinline__ void mlp_commit(const B2BParams& p, f32x4_t (&t)[TM * N2 / 4 / NT], int bz, int rbs, int rb,
+                                           int cn, int c, int m0, volatile int* flag) {
+  constexpr int QPR = N2 / 4;                          // column quads per row
+  constexpr int QUADS = TM * QPR / NT;                 // quads per thread
+  static_assert(NT % QPR == 0, "a thread's column quad is the same in every step");
+  constexpr int kSc1 = 16;                             // cache policy: device-coherent
+  const int tid = threadIdx.x, q4 = tid % QPR;
+  float* part = p.ws_part + (int64_t)bz * cn * p.M * N2;
+  const int rows = min(TM, p.M - m0);
+  // Buffer resource over chunk k's partial rows [m0, m0 + rows): raw 32-bit
+  // data; accesses past its end are dropped (stores) or read as 0 (loads).
+  auto part_rsrc = [&](int k) {
+    return __builtin_amdgcn_make_buffer_rsrc(part + ((int64_t)k * p.M + m0) * N2, 0, rows * N2 * 4, 0x00020000);
+  };
+  if (cn > 1) {
+    // publish O_c, then count this workgroup's arrival
+    const auto mine = part_rsrc(c);
+#pragma unroll
+    for (int j = 0; j < QUADS; ++j) {
+      const int r = (tid + j * NT) / QPR;
+      if (r < rows)
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, t[j]), mine, (r * QPR + q4) * 16, 0, kSc1);
+    }
+    wait_vmcnt<0>();          // this wave's partial stores have completed
+    __syncthreads();          // ... and every wave's
+    if (tid == 0) {
+      unsigned* cnt = p.ws_count + (int64_t)bz * rbs + rb;
+      const unsigned old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = old == (unsigned)(cn - 1);
+      if (last) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
+      *flag = last;
+    }
+    __syncthreads();
+    if (!*flag) return;       // the last workgroup of the row block commits
+  }
+
+  // O = O_0 + O_1 + ... (chunk order, whichever workgroup finished last; its
+  // own partial comes from its registers, equal to what it stored) + b2, output
+  // ReLU, bf16 rows.  A thread's column quad is the same in every step, so b2 is
+  // read once; another chunk's partials are loaded for all steps before any is
+  // used, so their latencies overlap.
+  uint16_t* O = p.O + (int64_t)bz * p.so;
+  f32x4_t bb = {0.0f, 0.0f, 0.0f, 0.0f};
+  if (p.b2) bb = *reinterpret_cast<const f32x4_t*>(p.b2 + 4 * q4);
+  if (cn > 1) {
+    f32x4_t acc2[QUADS];
+    for (int k = 0; k < cn; ++k) {
+      if (k == c) {
+#pragma unroll
+        for (int j = 0; j < QUADS; ++j) acc2[j] = k == 0 ? t[j] : acc2[j] + t[j];
+        continue;
+      }
+      const auto src = part_rsrc(k);
+      u32x4_t w[QUADS];
+#pragma unroll
+      for (int j = 0; j < QUADS; ++j) {
+        const int r = min((tid + j * NT) / QPR, rows - 1);
+        w[j] = __builtin_amdgcn_raw_buffer_load_b128(src, (r * QPR + q4) * 16, 0, kSc1);
+      }
+#pragma unroll
+      for (int j = 0; j < QUADS; ++j) {
+        const f32x4_t v = __builtin_bit_cast(f32x4_t, w[j]);
+        acc2[j] = k == 0 ? v : acc2[j] + v;
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < QUADS; ++j) t[j] = acc2[j];
+  }
+#pragma unroll
+  for (int j = 0; j < QUADS; ++j) {
+    const int m = m0 + (tid + j * NT) / QPR;
+    if (m >= p.M) continue;
+    f32x4_t y = t[j];
+    if (p.b2) y += bb;
+    if (p.out_relu)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) y[e] = fmaxf(y[e], 0.0f);
+    const u32x2_t o2 = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
+    __builtin_nontemporal_store(o2, reinterpret_cast<u32x2_t*>(O + (int64_t)m * p.ldo + 4 * q4));
+  }
+}
+
 template <int N2>
 __global__ __launch_bounds__(MlpS::NT, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
 void b2b_mlp_kernel(B2BParams p) {
@@ -204,95 +293,12 @@ void b2b_mlp_kernel(B2BParams p) {
   }
   __syncthreads();
 
-  // ---- Epi2 (commit) over the row-major tile: thread t handles the column
-  // quad (t + 256 j) % QPR of row (t + 256 j) / QPR, so every wave-wide
-  // access covers two whole rows: 1 KB of partials, 512 bytes of O.
-  // The partials go through memory with device-coherent 16-byte accesses
-  // (sc1): the workgroups of a row block need not share an XCD, and the
-  // reader reads only after the writer's stores completed (arrival count).
-  constexpr int QPR = N2 / 4;                          // column quads per row
-  constexpr int QUADS = S::TM * QPR / S::NT;           // quads per thread
-  static_assert(S::NT % QPR == 0, "a thread's column quad is the same in every step");
-  constexpr int kSc1 = 16;                             // cache policy: device-coherent
-  const int q4 = tid % QPR;
-  auto quad_lds = [&](int j) { return *reinterpret_cast<const f32x4_t*>(pt_at((tid + j * S::NT) / QPR, q4)); };
-  float* part = p.ws_part + (int64_t)bz * cn * p.M * N2;
-  const int rows = min(S::TM, p.M - m0);
-  // Buffer resource over chunk k's partial rows [m0, m0 + rows): raw 32-bit
-  // data; accesses past its end are dropped (stores) or read as 0 (loads).
-  auto part_rsrc = [&](int k) {
-    return __builtin_amdgcn_make_buffer_rsrc(part + ((int64_t)k * p.M + m0) * N2, 0, rows * N2 * 4, 0x00020000);
-  };
-  if (cn > 1) {
-    // publish O_c, then count this workgroup's arrival
-    const auto mine = part_rsrc(c);
-#pragma unroll 8
-    for (int j = 0; j < QUADS; ++j) {
-      const int r = (tid + j * S::NT) / QPR;
-      if (r < rows)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, quad_lds(j)), mine, (r * QPR + q4) * 16, 0,
-                                               kSc1);
-    }
-    wait_vmcnt<0>();          // this wave's partial stores have completed
-    __syncthreads();          // ... and every wave's
-    if (tid == 0) {
-      unsigned* cnt = p.ws_count + (int64_t)bz * (gridDim.x / cn) + rb;
-      const unsigned old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const int last = old == (unsigned)(cn - 1);
-      if (last) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-      last_flag = last;
-    }
-    __syncthreads();
-    if (!last_flag) return;   // the last workgroup of the row block commits
-  }
-
-  // O = O_0 + O_1 + ... (chunk order, whichever workgroup finished last; its
-  // own partial comes from LDS, equal to what it stored) + b2, output ReLU,
-  // bf16 rows.  A thread's column quad is the same in every step, so b2 is
-  // read once; the other chunks' partials are loaded for all steps before
-  // any is used, so their latencies overlap.
-  uint16_t* O = p.O + (int64_t)bz * p.so;
-  f32x4_t bb = {0.0f, 0.0f, 0.0f, 0.0f};
-  if (p.b2) bb = *reinterpret_cast<const f32x4_t*>(p.b2 + 4 * q4);
+  // ---- Epi2 over the row-major tile
+  constexpr int QPR = N2 / 4, QUADS = S::TM * QPR / S::NT;
   f32x4_t t[QUADS];
 #pragma unroll
-  for (int j = 0; j < QUADS; ++j) t[j] = quad_lds(j);
-  if (cn > 1) {
-    f32x4_t acc2[QUADS];
-    for (int k = 0; k < cn; ++k) {
-      if (k == c) {
-#pragma unroll
-        for (int j = 0; j < QUADS; ++j) acc2[j] = k == 0 ? t[j] : acc2[j] + t[j];
-        continue;
-      }
-      const auto src = part_rsrc(k);
-      u32x4_t w[QUADS];
-#pragma unroll
-      for (int j = 0; j < QUADS; ++j) {
-        const int r = min((tid + j * S::NT) / QPR, rows - 1);
-        w[j] = __builtin_amdgcn_raw_buffer_load_b128(src, (r * QPR + q4) * 16, 0, kSc1);
-      }
-#pragma unroll
-      for (int j = 0; j < QUADS; ++j) {
-        const f32x4_t v = __builtin_bit_cast(f32x4_t, w[j]);
-        acc2[j] = k == 0 ? v : acc2[j] + v;
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < QUADS; ++j) t[j] = acc2[j];
-  }
-#pragma unroll
-  for (int j = 0; j < QUADS; ++j) {
-    const int m = m0 + (tid + j * S::NT) / QPR;
-    if (m >= p.M) continue;
-    f32x4_t y = t[j];
-    if (p.b2) y += bb;
-    if (p.out_relu)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) y[e] = fmaxf(y[e], 0.0f);
-    const u32x2_t o2 = {pack_bf16x2(y[0], y[1]), pack_bf16x2(y[2], y[3])};
-    __builtin_nontemporal_store(o2, reinterpret_cast<u32x2_t*>(O + (int64_t)m * p.ldo + 4 * q4));
-  }
+  for (int j = 0; j < QUADS; ++j) t[j] = *reinterpret_cast<const f32x4_t*>(pt_at((tid + j * S::NT) / QPR, tid % QPR));
+  mlp_commit<S::TM, S::NT, N2>(p, t, bz, gridDim.x / cn, rb, cn, c, m0, &last_flag);
 }
 
 // Whole-row-block form: one workgroup per 128-row block runs the N1 / 256
@@ -750,19 +756,229 @@ void b2b_mlp_wide_kernel(B2BParams p) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Few rows.  On 128-row blocks a batch of a few thousand rows leaves most CUs
+// without a workgroup, and the ring's barriers make each k step wait for the
+// slowest of its loads.  Here a workgroup owns 32 rows and 256 UPW hidden units;
+// its four waves take units of 64 hidden (wave w: w, w + 4) and run both products for them
+// on their own.  The rows of X (at most 1024 wide) stay in LDS, the only thing the
+// waves share; the weights stream through a ring of S stages per wave, each stage
+// 64 rows x 128 bytes (whole lines): K / 64 stages of W1^T, then two of W2^T (64
+// output rows, the unit's 64 hidden each).  No barrier between the arrival of X and
+// the sum of the waves' O tiles (in wave order, through LDS).  What bounds it is the CU's
+// load path: 512 K + 64 KB of weights per 256 hidden units (1 KB per about 32 cycles).
+// The register hand-off of S is the 128-row kernels'.
+// ---------------------------------------------------------------------------
+constexpr int kMlpRowsLds = 160 * 1024;
+template <int UPW, int S>
+struct MlpFew {
+  static constexpr int TM = 32, NW = 4, NT = 64 * NW, N2 = 128;
+  static constexpr int STAGE = 64 * 128, RING = S * STAGE, OFF_X = NW * RING;
+  static constexpr int MAX_K = (kMlpRowsLds - OFF_X) / (TM * 2);
+  static constexpr int PITCH = N2 * 4 + 16, TILE = TM * PITCH;   // one wave's O tile
+  static_assert(NW * TILE + 16 <= OFF_X, "O tiles and the flag over the rings");
+};
+
+template <int UPW, int S>
+__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void b2b_mlp_few_kernel(B2BParams p) {
+  using F = MlpFew<UPW, S>;
+  __shared__ __attribute__((aligned(16))) char smem[kMlpRowsLds];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lr = lane & 31, lg = lane >> 5;
+  const int cn = p.cn, c = blockIdx.x % cn, rb = blockIdx.x / cn;
+  const int bz = blockIdx.y, m0 = rb * F::TM;
+  const int KT = p.K / 64, SPU = KT + 2, n_st = UPW * SPU;
+  const int h0 = c * 256 * UPW + 64 * wave;       // the wave's unit u: hidden h0 + 256 u .. + 63
+  const char* W1 = reinterpret_cast<const char*>(p.W1 + (int64_t)bz * p.sw1 + (int64_t)h0 * p.ldw1);
+  const char* W2 = reinterpret_cast<const char*>(p.W2 + (int64_t)bz * p.sw2 + h0);
+
+  // b1 in accumulator order: elements 8 s .. 8 s + 7 of block bn hold hidden
+  // units 32 bn + 16 s + 8 lg + 0..7 of the unit.
+  f32x4_t b1v[UPW][8] = {};
+  if (p.b1) {
+#pragma unroll
+    for (int u = 0; u < UPW; ++u)
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        b1v[u][i] = *reinterpret_cast<const f32x4_t*>(p.b1 + h0 + 256 * u + 32 * (i >> 2) + 16 * ((i >> 1) & 1) +
+                                                      8 * lg + 4 * (i & 1));
+  }
+
+  // A wave-wide load fills 8 rows of 128 bytes: row r, 16-byte chunk c at position
+  // c ^ ((r >> 1) & 7) (conflict-free fragment reads).  X: 64-wide k blocks of 32
+  // rows (4 KB), the wave loads rows 8 wave .. + 7 of each.
+  const int r8 = lane >> 3, ch = (lane & 7) ^ (lane >> 4);
+  {
+    const char* xg = reinterpret_cast<const char*>(p.X + (int64_t)bz * p.sx +
+                                                   (int64_t)min(m0 + 8 * wave + r8, p.M - 1) * p.ldx) +
+                     (ch ^ ((wave & 1) << 2)) * 16;
+    char* dst = smem + F::OFF_X + wave * 1024;
+    for (int kb = 0; kb < KT; ++kb) dma16(xg + 128 * kb, dst + 4096 * kb);
+  }
+  // Load j (rows 8 j .. + 7) of a stage.  W1^T: the rows of each 32-row block are
+  // taken with bits 2 and 3 of the row swapped, so load j starts at row
+  // 16 (j / 2) + 4 (j % 2) and the lane's bit 2 counts 8; W2^T: row 8 j.
+  char* const ring = smem + wave * F::RING;
+  const uint32_t ring0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)ring);
+  const int64_t p1 = 2 * p.ldw1, p2 = 2 * p.ldw2;
+  const uint32_t l1 = (uint32_t)(((r8 & 3) | ((r8 & 4) << 1)) * p1), l2 = (uint32_t)(r8 * p2);
+  struct Src {
+    const char* base;
+    int64_t d16, dodd;
+    uint32_t l;
+  };
+  int nu = 0, nq = 0, issued = 0;                 // the next stage to load
+  auto next = [&]() __attribute__((always_inline)) {
+    const bool first = nq < KT;
+    const int64_t pitch = first ? p1 : p2;
+    Src s{first ? W1 + 256 * nu * p1 + 128 * nq : W2 + 64 * (nq - KT) * p2 + 512 * nu, 16 * pitch,
+          (first ? 4 : 8) * pitch, first ? l1 : l2};
+    ++issued;
+    if (++nq == SPU) nq = 0, ++nu;
+    return s;
+  };
+  auto load = [&](const Src& s, int slot, int j) __attribute__((always_inline)) {
+    dma16(s.base + (j >> 1) * s.d16 + (j & 1) * s.dodd + (s.l + (uint32_t)(ch ^ ((j & 1) << 2)) * 16),
+          ring + slot * F::STAGE + j * 1024);
+  };
+#pragma unroll
+  for (int st = 0; st < S; ++st) {                // n_st > S: K >= 128
+    const Src s = next();
+#pragma unroll
+    for (int j = 0; j < 8; ++j) load(s, st, j);
+  }
+  wait_vmcnt<8 * S>();
+  lds_barrier();                                  // X is in LDS
+
+  f32x16_t O[4], P[2];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) O[b][i] = 0.0f;
+  const int sw = (lr >> 1) & 7;
+  const uint32_t x0 = (uint32_t)reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) char*)smem) + F::OFF_X;
+  uint32_t fa[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) fa[ks] = lr * 128 + (((2 * ks + lg) ^ sw) << 4);
+  u32x4_t f[2][4], x[1][4];
+  int st = 0, slot = 0;
+  // Fragments of the oldest stage; its slot then takes stage st + S, whose loads
+  // go between the MFMAs.
+  auto open = [&]() __attribute__((always_inline)) {
+    const int after = n_st - 1 - st;              // at most S - 1 stages are in flight behind st
+    if (after >= S - 1) wait_vmcnt<8 * (S - 1)>();
+    else if (after == 2) wait_vmcnt<16>();
+    else if (after == 1) wait_vmcnt<8>();
+    else wait_vmcnt<0>();
+    uint32_t a[4];
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) a[ks] = ring0 + slot * F::STAGE + fa[ks];
+    read_blocks(f, a);
+  };
+  auto products = [&](f32x16_t& d0, f32x16_t& d1, const u32x4_t (&b)[4]) __attribute__((always_inline)) {
+    const bool more = issued < n_st;
+    Src s{};
+    if (more) s = next();
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      Mma<bf16_t>::run(i & 1 ? d1 : d0, f[i & 1][i >> 1], b[i >> 1]);
+      __builtin_amdgcn_sched_barrier(0);
+      if (more) load(s, slot, i);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    ++st;
+    if (++slot == S) slot = 0;
+  };
+#pragma unroll
+  for (int u = 0; u < UPW; ++u) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) P[i >> 2][4 * (i & 3) + e] = b1v[u][i][e];
+#pragma unroll 1
+    for (int kb = 0; kb < KT; ++kb) {             // P^T += W1^T X^T
+      open();
+      uint32_t a[4];
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) a[ks] = x0 + kb * 4096 + fa[ks];
+      read_blocks(x, a);
+      products(P[0], P[1], x[0]);
+    }
+    u32x4_t sf[4];                                // S = ReLU(P): k step 2 bn + s of the second product
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        sf[i][e] = pack_bf16x2(fmaxf(P[i >> 1][8 * (i & 1) + 2 * e], 0.0f), fmaxf(P[i >> 1][8 * (i & 1) + 2 * e + 1], 0.0f));
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {                 // O^T += W2^T S^T, output rows 64 h .. + 63
+      open();
+      products(O[2 * h], O[2 * h + 1], sf);
+    }
+  }
+
+  __syncthreads();   // every wave is done with its ring
+  {
+    char* dst = smem + wave * F::TILE + lr * F::PITCH + 16 * lg;
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<f32x4_t*>(dst + (32 * b + 8 * g) * 4) =
+            f32x4_t{O[b][4 * g], O[b][4 * g + 1], O[b][4 * g + 2], O[b][4 * g + 3]};
+  }
+  __syncthreads();
+  f32x4_t t[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const char* src = smem + ((tid >> 5) + 8 * j) * F::PITCH + (tid & 31) * 16;
+    t[j] = *reinterpret_cast<const f32x4_t*>(src);
+#pragma unroll
+    for (int w = 1; w < F::NW; ++w) t[j] += *reinterpret_cast<const f32x4_t*>(src + w * F::TILE);
+  }
+  mlp_commit<F::TM, F::NT, F::N2>(p, t, bz, gridDim.x / cn, rb, cn, c, m0,
+                                  reinterpret_cast<volatile int*>(smem + F::NW * F::TILE));
+}
+
 bool b2b_mlp_supported(int K, int N1, int N2) {
   return N2 == 128 && N1 % kMlpHidden == 0 && N1 > 0 && K % 64 == 0 && K / 64 >= MlpS::STAGES - 1;
 }
 
 hipError_t launch_b2b_mlp(const B2BParams& p, hipStream_t st) {
   if (!b2b_mlp_supported(p.K, p.N1, p.N2) || (p.cn != 1 && p.cn != p.N1 / kMlpHidden)) return hipErrorInvalidValue;
+  // 32-row workgroups of 256 hidden units while they fit one generation of 256 CUs
+  // (each streams its share of the weights), of 512 while those do; K limited by X in
+  // LDS.  Without the split's workspace a row block is one workgroup.  Measured (us,
+  // this form / 128-row forms, K x N1): 1 row 256 x 256 5.6 / 10.5, 1024 x 512 12.3 / 20.1;
+  // 1000 rows 512 x 512 10.6 / 18.7; 4000 rows 1024 x 512 16.7 / 24.3; with two units a wave:
+  // 8000 rows 256 x 512 9.7 / 17.5, 1024 x 512 22.0 / 25.3, 4000 rows 1024 x 1024 24.5 / 26.6.  A
+  // second generation (or a third unit a wave) costs more than the 128-row forms.
+  const int cn_all = p.N1 / kMlpHidden;
+  const int64_t few_rbs = (p.M + 31) / 32;
+  const bool single = p.K <= 1024 && (cn_all == 1 || p.cn > 1) && few_rbs * p.batch * cn_all <= 256;
+  const bool pairs = p.K <= 1024 && cn_all % 2 == 0 && (cn_all == 2 || p.cn > 1) && few_rbs * p.batch * cn_all <= 512;
+  if (single || pairs) {
+    B2BParams q = p;
+    q.cn = single ? cn_all : cn_all / 2;
+    const dim3 grid((unsigned)(few_rbs * q.cn), (unsigned)q.batch), block(256);
+    if (single) {
+      if (q.K <= 512) hipLaunchKernelGGL((b2b_mlp_few_kernel<1, 4>), grid, block, 0, st, q);
+      else hipLaunchKernelGGL((b2b_mlp_few_kernel<1, 3>), grid, block, 0, st, q);
+    } else {
+      if (q.K <= 512) hipLaunchKernelGGL((b2b_mlp_few_kernel<2, 4>), grid, block, 0, st, q);
+      else hipLaunchKernelGGL((b2b_mlp_few_kernel<2, 3>), grid, block, 0, st, q);
+    }
+    return hipGetLastError();
+  }
   const unsigned rbs = (unsigned)((p.M + kMlpRows - 1) / kMlpRows);
   // N1 = 512: the wide form for every whole row block, and also where the chunks
   // would be split but K is short: a workgroup then has little to stream, and the
   // split form's commit costs more than the idle CUs.  Measured at N1 = 512 (us,
-  // wide / split): 4000 x 256 14.5 / 16.5, 16384 x 512 19.8 / 23.0, 4000 x 512 19.2 / 19.1,
-  // 16384 x 1024 29.3 / 29.7, 4000 x 1024 28.5 / 24.3; against the chunked whole form:
-  // 65536 x 1024 77.8 / 92 on one box (90.6 / 101 on another), 65536 x 256 33.7 / 45.7.
+  // wide / split): 16384 x 256 15.1 / 20.2, 16384 x 512 19.8 / 23.0, 16384 x 1024 29.3 / 29.7;
+  // against the chunked whole form: 65536 x 1024 77.8 / 92 on one box (90.6 / 101 on another),
+  // 65536 x 256 33.7 / 45.7.
   const bool wide = p.N1 == 512 && (p.cn == 1 || p.K <= 512);
   const dim3 grid(rbs * (unsigned)(wide ? 1 : p.cn), (unsigned)p.batch), block(MlpS::NT);
   if (wide) hipLaunchKernelGGL((b2b_mlp_wide_kernel<128>), grid, dim3(512), 0, st, p);

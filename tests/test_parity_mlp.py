@@ -165,23 +165,71 @@ def test_mlp_batched(shared_w1, shared_w2):
         assert_close_bf16(got[b], ref, f"MLP batch entry {b}")
 
 
+def _check_mlp(batch, M, K, N1, out_relu, pad=0, with_b1=True, ws=None):
+    """Every element against fp64 on the GPU; pad: elements added to every row pitch."""
+    g = torch.Generator(device="cuda").manual_seed(M + K + N1)
 
-@pytest.mark.parametrize("out_relu", [False, True])
-@pytest.mark.parametrize("batch,M,K", [(1, 32769, 128), (1, 32897, 192), (1, 33000, 1024), (3, 300, 320), (1, 1, 512)])
-def test_mlp_wide_form(batch, M, K, out_relu):
-    """N1 = 512 in one pass (128 x 512 products): two, three, five, eight and sixteen k steps (the ring of nine pieces
-    starts at different places), one row past a row block, batches; every element against fp64 on the GPU."""
-    g = torch.Generator(device="cuda").manual_seed(M + K)
-    rnd = lambda *sh, std=1.0: torch.randn(sh, generator=g, device="cuda") * std
-    X = rnd(batch, M, K).bfloat16()
-    W1, W2 = rnd(512, K, std=K ** -0.5).bfloat16(), rnd(128, 512, std=512 ** -0.5).bfloat16()
-    b1, b2 = rnd(512, std=0.5), rnd(128, std=0.5)
-    Y = cf.b2b_mlp(X, W1, b1, W2, b2, out_relu=out_relu)
+    def rnd(*sh, std=1.0):
+        t = torch.full(sh[:-1] + (sh[-1] + pad,), float("nan"), device="cuda", dtype=torch.bfloat16)
+        t[..., :sh[-1]] = (torch.randn(sh, generator=g, device="cuda") * std).bfloat16()
+        return t[..., :sh[-1]]
+
+    X, W1, W2 = rnd(batch, M, K), rnd(N1, K, std=K ** -0.5), rnd(128, N1, std=N1 ** -0.5)
+    b1 = torch.randn(N1, generator=g, device="cuda") * 0.5 if with_b1 else None
+    b2 = torch.randn(128, generator=g, device="cuda") * 0.5
+    out = torch.full((batch, M, 128 + pad), 7.0, device="cuda", dtype=torch.bfloat16)
+    Y = cf.b2b_mlp(X, W1, b1, W2, b2, out_relu=out_relu, out=out[..., :128], ws=ws)
     torch.cuda.synchronize()
-    s = torch.relu(X.double().reshape(-1, K) @ W1.double().t().contiguous() + b1.double())
+    s = torch.relu(X.double().reshape(-1, K) @ W1.double().t().contiguous() + (b1.double() if with_b1 else 0.0))
     o = s @ W2.double().t().contiguous() + b2.double()
     o = torch.relu(o) if out_relu else o
     err = Y.double().reshape(-1, 128) - o
     # the suite's bf16 bounds, the largest error scaled with the largest value (an ulp at 4 is 2^-6)
     assert float(err.square().sum().sqrt() / o.square().sum().sqrt()) < 5e-3
     assert float((err.abs() / o.abs().clamp(min=1.0)).max()) < 2e-2
+    assert bool((out[..., 128:] == 7.0).all())
+    return Y
+
+
+@pytest.mark.parametrize("out_relu", [False, True])
+@pytest.mark.parametrize("batch,M,K", [(1, 32769, 128), (1, 32897, 192), (1, 33000, 1024), (3, 2800, 320),
+                                       (1, 8193, 512)])
+def test_mlp_wide_form(batch, M, K, out_relu):
+    """N1 = 512 in one pass (128 x 512 products): two, three, five, eight and sixteen k steps (the ring of nine pieces
+    starts at different places), one row past a row block, batches."""
+    _check_mlp(batch, M, K, 512, out_relu)
+
+
+@pytest.mark.parametrize("batch,M,K,N1,pad", [
+    (1, 1, 128, 256, 0), (1, 31, 192, 256, 8), (1, 33, 512, 256, 0), (2, 65, 576, 256, 0), (1, 8192, 128, 256, 0),
+    (1, 40, 1024, 512, 8), (1, 4096, 256, 512, 0), (1, 4097, 640, 512, 0), (1, 8192, 1024, 512, 0),
+    (3, 97, 320, 768, 8), (1, 2049, 512, 1024, 0), (1, 4096, 1024, 1024, 0), (1, 1, 1024, 2560, 0)])
+def test_mlp_few_rows(batch, M, K, N1, pad):
+    """32-row workgroups: one and two units of 64 hidden per wave, one workgroup and several (even and odd counts) per
+    row block, the shortest K, the last K of the deep ring and the first and last of the other, ragged rows, pitches
+    beyond the row; the same bits again, counters back at zero; and without b1."""
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+    first = _check_mlp(batch, M, K, N1, False, pad, ws=ws).clone()
+    again = _check_mlp(batch, M, K, N1, False, pad, ws=ws)
+    assert torch.equal(first.view(torch.int16), again.view(torch.int16))
+    assert int(ws[:cf.CF_B2B_WS_HEADER_BYTES].view(torch.int32).abs().sum().item()) == 0
+    _check_mlp(batch, M, K, N1, True, pad, with_b1=False)
+
+
+@pytest.mark.parametrize("M,K,N1", [(8193, 128, 256), (33, 1088, 256), (4097, 256, 1024), (8193, 1024, 512)])
+def test_mlp_past_the_few_rows_rule(M, K, N1):
+    _check_mlp(1, M, K, N1, False)
+
+
+def test_mlp_few_rows_special_values():
+    """Infinite and NaN inputs act on their own rows only, as in the forms for more rows."""
+    X = torch.randn(8192 + 64, 256, device="cuda").bfloat16()
+    X[3, 5], X[40, 0], X[41, 255] = float("inf"), float("nan"), float("-inf")
+    W1, W2 = torch.randn(256, 256, device="cuda").bfloat16(), torch.randn(128, 256, device="cuda").bfloat16()
+    b1 = torch.zeros(256, device="cuda")
+    few, many = cf.b2b_mlp(X[:64], W1, b1, W2), cf.b2b_mlp(X, W1, b1, W2)[:64]
+    torch.cuda.synchronize()
+    assert torch.equal(torch.isnan(few), torch.isnan(many))
+    assert torch.equal(torch.isinf(few), torch.isinf(many))
+    fin = torch.isfinite(many)
+    assert float((few[fin].float() - many[fin].float()).abs().max() / many[fin].float().abs().max()) < 1e-2
