@@ -55,15 +55,15 @@ struct MlpLayout {
   static_assert(W2_LOADS % MlpS::NW == 0, "W2 loads per wave");
 };
 
-// Commit of a TM x N2 row-major tile held as column quads: thread t holds the
+// Commit of a TM x N2 row-major tile by column quads: quad(j) gives thread t the
 // quad (t + NT j) % QPR of row (t + NT j) / QPR, so every wave-wide access
 // covers whole rows.  cn workgroups (c of them) share the rows; the partials
 // go through memory with device-coherent 16-byte accesses (sc1): the
 // workgroups of a row block need not share an XCD, and the reader reads only
 // after the writer's stores completed (arrival count).
-template <int TM, int NT, int N2>
-__device__ __forceinline__ void mlp_commit(const B2BParams& p, f32x4_t (&t)[TM * N2 / 4 / NT], int bz, int rbs, int rb,
-                                           int cn, int c, int m0, volatile int* flag) {
+template <int TM, int NT, int N2, typename Quad>
+__device__ __forceinline__ void mlp_commit(const B2BParams& p, Quad&& quad, int bz, int rbs, int rb,
+                                           int cn, int c, int m0, int& flag) {
   constexpr int QPR = N2 / 4;                          // column quads per row
   constexpr int QUADS = TM * QPR / NT;                 // quads per thread
   static_assert(NT % QPR == 0, "a thread's column quad is the same in every step");
@@ -79,11 +79,11 @@ __device__ __forceinline__ void mlp_commit(const B2BParams& p, f32x4_t (&t)[TM *
   if (cn > 1) {
     // publish O_c, then count this workgroup's arrival
     const auto mine = part_rsrc(c);
-#pragma unroll
+#pragma unroll 8
     for (int j = 0; j < QUADS; ++j) {
       const int r = (tid + j * NT) / QPR;
       if (r < rows)
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, t[j]), mine, (r * QPR + q4) * 16, 0, kSc1);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4_t, quad(j)), mine, (r * QPR + q4) * 16, 0, kSc1);
     }
     wait_vmcnt<0>();          // this wave's partial stores have completed
     __syncthreads();          // ... and every wave's
@@ -92,20 +92,23 @@ __device__ __forceinline__ void mlp_commit(const B2BParams& p, f32x4_t (&t)[TM *
       const unsigned old = __hip_atomic_fetch_add(cnt, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       const int last = old == (unsigned)(cn - 1);
       if (last) __hip_atomic_store(cnt, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // ready for the next call
-      *flag = last;
+      flag = last;
     }
     __syncthreads();
-    if (!*flag) return;       // the last workgroup of the row block commits
+    if (!flag) return;        // the last workgroup of the row block commits
   }
 
   // O = O_0 + O_1 + ... (chunk order, whichever workgroup finished last; its
-  // own partial comes from its registers, equal to what it stored) + b2, output
+  // own partial comes from its tile, equal to what it stored) + b2, output
   // ReLU, bf16 rows.  A thread's column quad is the same in every step, so b2 is
   // read once; another chunk's partials are loaded for all steps before any is
   // used, so their latencies overlap.
   uint16_t* O = p.O + (int64_t)bz * p.so;
   f32x4_t bb = {0.0f, 0.0f, 0.0f, 0.0f};
   if (p.b2) bb = *reinterpret_cast<const f32x4_t*>(p.b2 + 4 * q4);
+  f32x4_t t[QUADS];
+#pragma unroll
+  for (int j = 0; j < QUADS; ++j) t[j] = quad(j);
   if (cn > 1) {
     f32x4_t acc2[QUADS];
     for (int k = 0; k < cn; ++k) {
@@ -294,11 +297,10 @@ void b2b_mlp_kernel(B2BParams p) {
   __syncthreads();
 
   // ---- Epi2 over the row-major tile
-  constexpr int QPR = N2 / 4, QUADS = S::TM * QPR / S::NT;
-  f32x4_t t[QUADS];
-#pragma unroll
-  for (int j = 0; j < QUADS; ++j) t[j] = *reinterpret_cast<const f32x4_t*>(pt_at((tid + j * S::NT) / QPR, tid % QPR));
-  mlp_commit<S::TM, S::NT, N2>(p, t, bz, gridDim.x / cn, rb, cn, c, m0, &last_flag);
+  constexpr int QPR = N2 / 4;
+  mlp_commit<S::TM, S::NT, N2>(
+      p, [&](int j) { return *reinterpret_cast<const f32x4_t*>(pt_at((tid + j * S::NT) / QPR, tid % QPR)); }, bz,
+      gridDim.x / cn, rb, cn, c, m0, last_flag);
 }
 
 // Whole-row-block form: one workgroup per 128-row block runs the N1 / 256
@@ -938,8 +940,8 @@ void b2b_mlp_few_kernel(B2BParams p) {
 #pragma unroll
     for (int w = 1; w < F::NW; ++w) t[j] += *reinterpret_cast<const f32x4_t*>(src + w * F::TILE);
   }
-  mlp_commit<F::TM, F::NT, F::N2>(p, t, bz, gridDim.x / cn, rb, cn, c, m0,
-                                  reinterpret_cast<volatile int*>(smem + F::NW * F::TILE));
+  mlp_commit<F::TM, F::NT, F::N2>(p, [&](int j) { return t[j]; }, bz, gridDim.x / cn, rb, cn, c, m0,
+                                  *reinterpret_cast<int*>(smem + F::NW * F::TILE));
 }
 
 bool b2b_mlp_supported(int K, int N1, int N2) {
