@@ -588,6 +588,10 @@ AttentionForm attention_form(int64_t M, int64_t batch, int64_t Lk, int d) {
   constexpr int64_t kCUs = 256;
   auto wgs = [&](int qg) { return (M + 32 * qg - 1) / (32 * qg) * batch; };
   AttentionForm f{0, 1};
+  // One key block in all: more waves and their merge only cost (kernel us, QG 1 or 2 /
+  // two per CU: 180 x 47 x 47 5.5 / 4.6, 8 x 300 x 64 5.2 / 4.6, 64 x 1 x 64 4.8 / 4.3; two blocks
+  // 5.4 / 5.4, 5.4 / 5.3, 4.8 / 5.1; at d = 128, 32 or 64 keys, 5.1 - 5.7 / 5.5 - 6.0).
+  if (d == 64 && Lk <= 64) return f;
   if (M <= 32 || wgs(1) <= kCUs) f.qg = 1;
   else if (M <= 64 || wgs(2) <= kCUs) f.qg = 2;
   else if (wgs(4) <= kCUs) f.qg = 4;
