@@ -588,13 +588,14 @@ AttentionForm attention_form(int64_t M, int64_t batch, int64_t Lk, int d) {
   constexpr int64_t kCUs = 256;
   auto wgs = [&](int qg) { return (M + 32 * qg - 1) / (32 * qg) * batch; };
   AttentionForm f{0, 1};
-  // One key block in all: more waves and their merge only cost (kernel us, QG 1 or 2 /
-  // two per CU: 180 x 47 x 47 5.5 / 4.6, 8 x 300 x 64 5.2 / 4.6, 64 x 1 x 64 4.8 / 4.3; two blocks
-  // 5.4 / 5.4, 5.4 / 5.3, 4.8 / 5.1; at d = 128, 32 or 64 keys, 5.1 - 5.7 / 5.5 - 6.0).
-  if (d == 64 && Lk <= 64) return f;
   if (M <= 32 || wgs(1) <= kCUs) f.qg = 1;
   else if (M <= 64 || wgs(2) <= kCUs) f.qg = 2;
   else if (wgs(4) <= kCUs) f.qg = 4;
+  // Few keys: the merge costs more than the groups save.  Kernel us, this form / two per
+  // CU: QG 4, 36 x 722 x 192 x 64 7.1 / 6.7, x 256 7.5 / 7.6; 128 x 185 x 192 x 128 10.1 / 9.0, x 256
+  // 10.5 / 10.4; QG 2, 16 x 800 x 128 x 64 5.6 / 5.6, x 192 6.0 / 6.4, 16 x 800 x 128 x 128 7.5 / 7.2,
+  // x 192 8.3 / 8.4; QG 1, 8 x 300 x 64 x 64 5.2 / 4.6, 16 x 300 x 96 x 64 5.1 / 5.3, x 64 x 128 5.6 / 6.0.
+  if (Lk <= (f.qg == 4 ? 192 : f.qg == 2 ? 128 : d == 64 ? 64 : 0)) return AttentionForm{0, 1};
   if (f.qg == 1) {
     const int64_t per_wave = (Lk + 31) / 32 / (d == 128 ? 4 : 8);   // key blocks of one wave, unsplit
     f.nz = (int)std::max<int64_t>(1, std::min<int64_t>({kCUs / wgs(1), per_wave / 2, 8}));

@@ -199,6 +199,8 @@ def test_attention_full_size_sampled_rows():
     (1, 9, 33, 290),     # two 32-query blocks
     (70, 4, 33, 129),    # 32 < Lq <= 64: two query waves, four key groups
     (5, 13, 250, 200),   # 195 64-query blocks
+    (70, 4, 33, 128),    # the same with the most keys that keep one group
+    (4, 16, 511, 192),   # and for four query waves
     (4, 16, 511, 321),   # 256 128-query blocks: two key groups, an odd number of key blocks
 ])
 def test_attention_key_groups(B, H, Lq, Lk, d):
