@@ -74,12 +74,10 @@ int resident_wgs(int idx) {
 
 hipError_t launch_gemm_rows(const GemmRowsParams& p, int idx, hipStream_t st) {
   const GemmKernel& k = table()[idx];
-  // 256-row tiles have one workgroup per tile, small tiles without row clusters
-  // a whole number of column tiles on each XCD, the others a whole number of
-  // row-block slots.
+  // 256-row tiles and small tiles without row clusters have one workgroup per
+  // tile, the others a whole number of row-block slots.
   unsigned wgs = (unsigned)(8 * p.slots * p.cn);
-  if (k.tm == 256) wgs = (unsigned)(p.num_rb * p.cn);
-  else if (k.epi == 3 && p.mode != ROWS_CLUSTER) wgs = (unsigned)(8 * ((p.cn + 7) / 8) * p.num_rb);
+  if (k.tm == 256 || (k.epi == 3 && p.mode != ROWS_CLUSTER)) wgs = (unsigned)(p.num_rb * p.cn);
   dim3 grid(wgs, (unsigned)p.batch);
   dim3 block((unsigned)k.threads);
   void* args[] = {const_cast<GemmRowsParams*>(&p)};
