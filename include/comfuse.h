@@ -238,18 +238,19 @@ cf_status cf_gemm_subgraph_noalloc(const cf_subgraph_args* a, void* hip_stream);
  * >= 128; b1 [N1] / b2 [N2] fp32 or NULL; out = CF_OUT_STORE or
  * CF_OUT_BIAS_RELU; R, gamma, beta NULL.  N1 is cut into chunks of 256
  * hidden units and the partial second products of the chunks are summed in
- * chunk order (the partial-sum identity of Sec. IV-A).  When
- * batch * ceil(M / 128) * N1 / 256 <= 256 (and N1 > 256), the chunks are
- * split over workgroups, one per chunk and 128-row block (the cross-CTA
- * dataflow of Sec. IV-A), and the last workgroup of a row block to finish
- * sums their partials at commit.  Otherwise one workgroup per row block runs
- * all chunks and keeps the sum in registers.
+ * a fixed order (the partial-sum identity of Sec. IV-A).  When
+ * batch * ceil(M / 128) * N1 / 256 <= 256 (and N1 > 256), a workspace is
+ * required and the chunks may be split over workgroups (the cross-CTA
+ * dataflow of Sec. IV-A); the last workgroup of a row block to finish sums
+ * their partials at commit.  Otherwise one workgroup per row block runs all
+ * chunks and keeps the sum in registers.  The bits of a result depend on the
+ * sizes only.
  * Workspace: 0 bytes for the FFN, for the MLP unless it splits the chunks, and
  * for attention unless it splits the keys (few queries against many keys:
  * several workgroups then take a part of the keys each and the last to finish
  * merges); then cf_b2bgemm_workspace() bytes, 16-byte aligned:
  * CF_B2B_WS_HEADER_BYTES of arrival counters (one 32-bit word per batch
- * entry and 128-row block, for attention 32-query block), then the fp32
+ * entry and row block), then the fp32
  * partial products.  The split MLP needs it (CF_ERR_WORKSPACE); attention
  * without it, or with a smaller one, keeps the keys in one workgroup.
  * Zero-fill the header once before the first call; every call leaves it all

@@ -871,13 +871,13 @@ cf_status cf_workspace_check(void* workspace, size_t ws_bytes, void* hip_stream)
   }
 }
 
-// MLP form.  The hidden chunks are split over workgroups (their partial
-// products meeting in the workspace) when the split grid fits one generation
-// of a 256-CU device, one workgroup per CU; otherwise one workgroup per row
-// block runs all chunks and needs no workspace.  Measured at K = 1024,
-// N1 = 512: split 28-32 us against 37-39 us at 96-128 row blocks, whole
-// 42-53 us against 51-62 us at 160-255.  The rule depends on the arguments
-// only.
+// Whether the MLP's hidden chunks may be split over workgroups (their partial
+// products meeting in the workspace): the grid of 128-row blocks and chunks
+// fits one generation of a 256-CU device.  The launch then chooses between the
+// split form, 32-row workgroups and the wide form; otherwise one workgroup per
+// row block runs all chunks and no workspace is needed.  Measured with the
+// chunked whole form, 160-255 row blocks at K = 1024, N1 = 512: whole 42-53 us, split
+// 51-62.  The rule depends on the arguments only.
 static constexpr int64_t kMlpSplitMaxWorkgroups = 256;
 static bool mlp_split(const cf_b2b_args* a) {
   return a->N1 > kMlpHidden &&

@@ -65,12 +65,15 @@ struct GemmRowsParams {
 // Each of the NW waves of the cn workgroups of a peer group adds
 // kArriveUnit / (cn * NW) to the group's counter once per tile, so a round
 // adds exactly kArriveUnit.  lcm(1..16) * 8 is divisible by cn * NW for every
-// cn <= 16 and NW in {1, 2, 4, 8}.
+// cn <= 16 and NW in {1, 2, 4, 8}; groups of more peers (small tiles, up to 32)
+// are planned only where the count divides it.
 constexpr unsigned long long kArriveUnit = 720720ull * 8ull;
 constexpr int kMaxSlots = 64;                        // concurrent peer groups
 // Exchange records: [stage 2][round parity 2][slot kMaxSlots][peer kRecPeers]
-// [row kRecRows] x 2 words (peer kRecLead: the leader's merged values).  A record's position depends only on (slot,
-// peer), never on the launch's peer count: round numbers grow per slot, so a
+// [row kRecRows] x 2 words (peer kRecLead: the leader's merged values; small tiles
+// put up to 32 peers of at most 64 rows into the same words of their slot).  A
+// record's position lies in its slot's words, whatever the launch's peer count:
+// round numbers grow per slot, so a
 // record left by an earlier call in a position only ever carries an older
 // round of the same slot (a position shared by different slots could hold
 // another slot's equal round number).  The parity of the round selects one

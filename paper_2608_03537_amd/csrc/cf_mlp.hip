@@ -31,6 +31,10 @@
 // needed.  The arrival counter of a row block goes back to 0 at the end of
 // the call (the last arriver resets it), so a zero-filled counter area stays
 // valid for every later call.
+//
+// This is the split form (b2b_mlp_kernel).  b2b_mlp_whole_kernel runs the chunks of
+// a row block in turn, b2b_mlp_wide_kernel all 512 hidden units at once, and
+// b2b_mlp_few_kernel works on 32-row blocks; launch_b2b_mlp chooses.
 #include "cf_gemm_tile.h"
 #include "comfuse.h"
 
