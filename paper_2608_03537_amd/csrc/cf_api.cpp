@@ -310,11 +310,16 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
     } else {
       return fail(CF_ERR_UNSUPPORTED, "unknown path %d", path);
     }
+    // Whole rows of the register-staged loop up to 384 wide keep several workgroups
+    // on a CU, so beyond one generation they stay: 14764 x 256 x 992 40 us, row clusters
+    // 55; 14764 x 384 x 496 33 / 38; 20000 x 128 x 1488 43 / 55 (6000 x 256 x 992 37 / 28).
+    const bool several = pl.kidx >= 0 && gemm_kernel(pl.kidx).loop == 0 && gemm_kernel(pl.kidx).tn <= 384 &&
+                         M > 32 * kAssumedCUs;
     // Fewer rows than fill the chip with 128-row tiles: 64 x 128 or small tiles,
     // as a row cluster or (row pass and second launch: about 4 us) small ones as
     // the plain product of the split path.  Only where the automatic choice already
     // takes a workspace, and not under an explicit path.
-    if (automatic && pl.kidx >= 0 && pl.mode == ROWS_LOCAL && use_optional) {
+    if (automatic && pl.kidx >= 0 && pl.mode == ROWS_LOCAL && use_optional && !several) {
       // Whole rows of 32 x TN on few CUs, or wide ones in many rounds: row
       // clusters if the caller gives a workspace and they are clearly faster.
       const double now = 0.85 * cost_whole(gemm_kernel(pl.kidx), M, K);
