@@ -187,6 +187,22 @@ __device__ __forceinline__ float tanh_exp(float z) {
   return copysignf((1.0f - t) * __builtin_amdgcn_rcpf(1.0f + t), z);
 }
 
+// exp(x - mx) = exp2(fma(x, sc, sh)) for the values x <= mx of a row, or of the part of one that a
+// tile holds.  mx is the part's maximum, raised to the lowest finite value first: the terms of a
+// part that is -infinity throughout are then 0 (they were NaN, here and in the merge of the parts).
+// Beyond 2.36e38 (masks of the type's lowest value) mx log2(e) overflows; values that large differ by
+// 2^103 at least where they differ, so any scale gives the same zeros and ones, and a power of two
+// leaves exactly 0 of x - mx at x = mx.
+constexpr float kLowestF32 = -3.4028234663852886e38f;
+struct SoftmaxExp {
+  float sc, sh;
+  __device__ __forceinline__ explicit SoftmaxExp(float mx) {
+    sc = fabsf(mx) > 2e38f ? 0.25f : 1.4426950408889634f;
+    sh = -mx * sc;
+  }
+  __device__ __forceinline__ float operator()(float x) const { return __builtin_amdgcn_exp2f(fmaf(x, sc, sh)); }
+};
+
 __device__ __forceinline__ void store4(void* base, int64_t off, int f32, const float (&v)[4]) {
   if (f32) {
     f32x4_t o = {v[0], v[1], v[2], v[3]};

@@ -415,11 +415,11 @@ void gemm_small_kernel(GemmRowsParams p) {
     if (e.softmax) {
       float mx = -INFINITY;
       each([&](float& v, int g, int) { mx = val[g] ? fmaxf(mx, v) : mx; });
-      mx = row_max<S::TPR>(mx);
-      const float nl = -mx * 1.4426950408889634f;
+      mx = fmaxf(row_max<S::TPR>(mx), kLowestF32);
+      const SoftmaxExp ex(mx);
       float t = 0.0f;
       each([&](float& v, int g, int) {
-        v = val[g] ? __builtin_amdgcn_exp2f(fmaf(v, 1.4426950408889634f, nl)) : 0.0f;
+        v = val[g] ? ex(v) : 0.0f;
         t += v;
       });
       float sm = row_sum<S::TPR>(t), f = 1.0f;

@@ -1313,7 +1313,8 @@ __device__ __forceinline__ void epilogue(f32x16_t (&x)[S::BM][S::BN], const EpiP
     wg_row_reduce<S, true>(mx, red, lane, wm, wn);
 #pragma unroll
     for (int bm = 0; bm < S::BM; ++bm) {
-      const float nl = -mx[bm] * 1.4426950408889634f;
+      mx[bm] = fmaxf(mx[bm], kLowestF32);
+      const SoftmaxExp ex(mx[bm]);
       float t = 0.0f;
 #pragma unroll
       for (int bn = 0; bn < S::BN; ++bn)
@@ -1322,7 +1323,7 @@ __device__ __forceinline__ void epilogue(f32x16_t (&x)[S::BM][S::BN], const EpiP
           const bool v = full_n || ncol(bn, g) < N;
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const float ev = v ? __builtin_amdgcn_exp2f(fmaf(x[bm][bn][4 * g + q], 1.4426950408889634f, nl)) : 0.0f;
+            const float ev = v ? ex(x[bm][bn][4 * g + q]) : 0.0f;
             x[bm][bn][4 * g + q] = ev;
             t += ev;
           }

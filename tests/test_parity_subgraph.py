@@ -371,3 +371,47 @@ def test_rowop_msts_grammar():
     cf.rowop(P, spec)
     torch.cuda.synchronize()
     assert_close_f32(host(Y), msts_ref(inp), "rowop MSTS")
+
+
+# (M, N, K, weight layout, dtype, path): the tile that each shape takes is named behind it
+MASKED_SOFTMAX = [
+    (128, 256, 256, "nk", "f32", 0),      # 32 x 32, clusters through an optional workspace
+    (256, 256, 512, "nk", "bf16", 0),     # the same in bf16
+    (300, 640, 272, "nk", "bf16", 0),     # 32 x 64
+    (300, 640, 272, "kn", "bf16", 0),
+    (999, 1024, 1040, "nk", "bf16", 0),   # 64 x 64
+    (1000, 512, 512, "nk", "bf16", 0),    # 64 x 128 on the direct-to-LDS ring
+    (1000, 768, 512, "kn", "bf16", 0),
+    (2047, 1024, 256, "nk", "bf16", 0),
+    (4096, 1024, 256, "nk", "bf16", 2),   # 128-row clusters, every peer merges
+    (600, 4096, 256, "nk", "bf16", 2),    # 16 peers, the leader merges
+    (150, 512, 400, "nk", "bf16", 1),     # whole rows, register-staged
+    (150, 256, 512, "nk", "bf16", 1),     # whole rows on the ring
+    (150, 2048, 512, "nk", "bf16", 3),    # split path
+]
+
+
+@pytest.mark.parametrize("value", ["inf", "lowest"])
+@pytest.mark.parametrize("M,N,K,layout,dtype,path", MASKED_SOFTMAX)
+def test_bias_masked_softmax(M, N, K, layout, dtype, path, value):
+    """A row softmax whose masked columns fill whole tiles, the first among them: they weigh 0 and the others what they
+    weigh without them.  Both sides form the logits from the same products, summed in fp32 (about 2^-24 sqrt(K) of a
+    logit of rms 1: 2e-6, 1e-5 allowed), exp2 and the division add a few 2^-24."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    X = torch.randn((M, K), generator=g, device="cuda").to(t)
+    W = (torch.randn((N, K) if layout == "nk" else (K, N), generator=g, device="cuda") * K ** -0.5).to(t)
+    low = -float("inf") if value == "inf" else torch.finfo(torch.float32).min
+    bias = torch.zeros(N, device="cuda")
+    bias[:N // 2], bias[-33:] = low, low
+    Y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    spec = [dict(kind=cf.CF_N_BIAS, v0=bias), dict(kind=cf.CF_N_SOFTMAX),
+            dict(kind=cf.CF_N_STORE, out=Y, ld=N, dtype=cf.CF_F32)]
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+    cf.gemm_subgraph(X, W, spec, w_layout=cf.CF_LAYOUT_NK if layout == "nk" else cf.CF_LAYOUT_KN, path=path, ws=ws,
+                     check=False)
+    cf.check_workspace(ws)
+    logits = X.double() @ (W.double().t().contiguous() if layout == "nk" else W.double())
+    ref = torch.softmax(logits + bias.double(), 1)
+    assert bool((Y[:, bias != 0] == 0).all())
+    assert float(((Y.double() - ref).abs() - 3e-5 * ref).max()) <= 0
