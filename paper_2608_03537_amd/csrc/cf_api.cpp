@@ -417,8 +417,8 @@ cf_status run_rows(const Plan& pl, GemmRowsParams p, void* ws, hipStream_t st) {
       cf_status s = hip_status(launch_gemm_rows(p, pl.kidx, st), "GEMM launch");
       return s != CF_OK ? s : hip_status(launch_row_kernel(f, st), "row pass launch");
     }
-    // The GEMM runs stage 1 only and publishes x and partial statistics.
-    p.epi.norm = NORM_NONE;
+    // The GEMM runs stage 1 only and publishes x and partial statistics (the
+    // norm stays: it chooses how stage 1 adds a staged residual).
     p.epi.act = ACT_NONE;
     p.epi.softmax = 0;
     p.epi.Y = nullptr;

@@ -1039,8 +1039,37 @@ __device__ __forceinline__ void epilogue(f32x16_t (&x)[S::BM][S::BN], const EpiP
           for (int q = 0; q < 4; ++q) x[bm][bn][4 * g + q] += bv[g][q];
     }
   }
-  if constexpr (STG) if (e.R) {
-    // The residual by two MFMAs per 32 x 32 block with an identity operand:
+  if constexpr (STG) if (e.R && e.norm != NORM_LAYER) {
+    // Element by element: in the product below an infinity or NaN (an additive
+    // mask, say) would meet the identity's zeros and reach the 15 other columns
+    // of its k step.  The chunks are read as there; lanes l and l + 32 swap halves
+    // of theirs: dword w of the first half then holds columns 16 h + 4 (l / 32) +
+    // 2 w, 2 w + 1 of the lane's row, of the second those 8 further.
+#pragma unroll
+    for (int bm = 0; bm < S::BM; ++bm) {
+      const int r = wm * S::WTM + bm * 32 + lr;
+      const char* rowp = r < S::STG_RA ? smem + r * S::TN * 2 : smem + S::V2_STAGE + (r - S::STG_RA) * S::TN * 2;
+#pragma unroll
+      for (int bn = 0; bn < S::BN; ++bn)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int cc = (wn * S::WTN + bn * 32) / 8 + 2 * h + lg;
+          const u32x4_t rv = lds_read16(rowp + ((cc ^ (r & 7)) << 4));
+#pragma unroll
+          for (int w = 0; w < 2; ++w) {
+            const auto t = __builtin_amdgcn_permlane32_swap(rv[w], rv[2 + w], false, false);
+#pragma unroll
+            for (int g = 0; g < 2; ++g) {
+              x[bm][bn][8 * h + 4 * g + 2 * w] += bf16_to_f32(t[g] & 0xFFFFu);
+              x[bm][bn][8 * h + 4 * g + 2 * w + 1] += bf16_to_f32(t[g] >> 16);
+            }
+          }
+        }
+    }
+  }
+  if constexpr (STG) if (e.R && e.norm == NORM_LAYER) {
+    // LayerNorm (a row that holds an infinity or NaN is NaN anyway): the
+    // residual by two MFMAs per 32 x 32 block with an identity operand:
     // D[n][m] += sum_k I[n][k] R[m][16h + k] adds R[m][n] for n in
     // [16h, 16h + 16) exactly (one non-zero product, rounded once into the
     // accumulator like a VALU add).  Lane l supplies the identity row n = l % 32

@@ -415,3 +415,28 @@ def test_bias_masked_softmax(M, N, K, layout, dtype, path, value):
     ref = torch.softmax(logits + bias.double(), 1)
     assert bool((Y[:, bias != 0] == 0).all())
     assert float(((Y.double() - ref).abs() - 3e-5 * ref).max()) <= 0
+
+
+@pytest.mark.parametrize("value", ["inf", "lowest"])
+@pytest.mark.parametrize("M,N,K,layout,dtype,path", MASKED_SOFTMAX)
+def test_causal_mask_softmax(M, N, K, layout, dtype, path, value):
+    """The same with an additive causal mask as the residual (the other half of the row masked in odd rows)."""
+    g = torch.Generator(device="cuda").manual_seed(M + N)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    X = torch.randn((M, K), generator=g, device="cuda").to(t)
+    W = (torch.randn((N, K) if layout == "nk" else (K, N), generator=g, device="cuda") * K ** -0.5).to(t)
+    keep = torch.arange(N, device="cuda")[None, :] <= (torch.arange(M, device="cuda") * N // M)[:, None]
+    keep[1::2] = keep[1::2].flip(1)
+    R = torch.zeros((M, N), device="cuda", dtype=t)
+    R[~keep] = -float("inf") if value == "inf" else torch.finfo(t).min
+    Y = torch.empty((M, N), dtype=torch.float32, device="cuda")
+    spec = [dict(kind=cf.CF_N_RESIDUAL, ld=N, dtype=cf._dt(R), **{"in": R}), dict(kind=cf.CF_N_SOFTMAX),
+            dict(kind=cf.CF_N_STORE, out=Y, ld=N, dtype=cf.CF_F32)]
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+    cf.gemm_subgraph(X, W, spec, w_layout=cf.CF_LAYOUT_NK if layout == "nk" else cf.CF_LAYOUT_KN, path=path, ws=ws,
+                     check=False)
+    cf.check_workspace(ws)
+    logits = X.double() @ (W.double().t().contiguous() if layout == "nk" else W.double())
+    ref = torch.softmax(torch.where(keep, logits, -float("inf")), 1)
+    assert bool((Y[~keep] == 0).all())
+    assert float(((Y.double() - ref).abs() - 3e-5 * ref).max()) <= 0
