@@ -236,13 +236,10 @@ def check_workspace(ws, stream=None):
 def _row_workspace(ws, need, device, stream, check):
     """The workspace to pass for a row call whose query answered ``need``.  An
     optional one is left out where using it would make the call synchronise
-    (``check``) or allocate while a graph is being captured."""
-    if need == CF_WS_OPTIONAL_BYTES:
-        if check:
-            return None
-        if ws is None and _capturing():
-            ws = _ws_cache.get((str(device), _stream(stream), "rows"))
-            return ws if ws is not None and ws.numel() >= need else None
+    (``check``), and in a graph capture unless the caller gives it: the graph
+    outlives what the cache holds (a larger call replaces it)."""
+    if need == CF_WS_OPTIONAL_BYTES and (check or (ws is None and _capturing())):
+        return None
     return workspace(need, device, stream) if ws is None else ws
 
 
@@ -476,22 +473,23 @@ def b2b_mlp(X, W1t, b1, W2t, b2=None, *, out_relu=False, out=None, ws=None, stre
 
 def _attention_workspace(a, device, stream):
     """The workspace of a call with few queries (it lets several workgroups
-    share a query block's keys), or None: the call then runs without it.
-    Nothing is allocated while a graph is being captured: there the zero-fill
-    would belong to the graph, and a later eager call would find it undone."""
+    share a query block's keys), or None: the call then runs without it, as it
+    does in a graph capture (the graph outlives what the cache holds: a larger
+    call replaces it)."""
     if a.batch * ((a.M + 31) // 32) >= 256:
         return None
     need = cf_b2bgemm_workspace(a)
-    if need == 0:
+    if need == 0 or _capturing():
         return None
-    if _capturing():
-        ws = _ws_cache.get((str(device), _stream(stream), "b2b"))
-        return ws if ws is not None and ws.numel() >= need else None
     return workspace(need, device, stream, kind="b2b")
 
 
-def b2b_attention(Q, K, V, scale=None, out=None, stream=None):
-    """O = softmax(scale * Q K^T) V for Q [B, H, Lq, d], K, V [B, H, Lk, d] (bf16, contiguous)."""
+def b2b_attention(Q, K, V, scale=None, out=None, stream=None, ws=None):
+    """O = softmax(scale * Q K^T) V for Q [B, H, Lq, d], K, V [B, H, Lk, d] (bf16, contiguous).
+
+    ws: a workspace of the caller's own, its first CF_B2B_WS_HEADER_BYTES zero,
+    for a call with few queries.  Without it an eager call takes a cached one
+    and a captured call keeps a query block's keys in one workgroup."""
     torch = _torch()
     B, H, Lq, d = Q.shape
     Lk = K.shape[2]
@@ -507,6 +505,7 @@ def b2b_attention(Q, K, V, scale=None, out=None, stream=None):
                   W2=_ptr(V), ldw2=d, sw2=Lk * d, w2_layout=CF_LAYOUT_KN,
                   out=CF_OUT_STORE, b2=None, R=None, ldr=0, sr=0, gamma=None, beta=None, eps=0.0,
                   O=_ptr(O), ldo=d, so=Lq * d)
-    ws = _attention_workspace(a, Q.device, stream)
+    if ws is None:
+        ws = _attention_workspace(a, Q.device, stream)
     _check(cf_b2bgemm(a, _ptr(ws), 0 if ws is None else ws.numel(), _stream(stream)))
     return O

@@ -118,3 +118,83 @@ def test_cluster_calls_of_different_widths_share_a_workspace():
         torch.cuda.synchronize()
         ref = O.postnorm(inp.X, inp.W, inp.bias, None, inp.gamma, inp.beta, 1.0, 1e-5)
         assert_close_f32(host(Y), ref, f"cluster {M}x{N} after other widths")
+
+
+def _captured(fn, stream):
+    """fn captured on `stream` (after two calls there that warm it up), and the graph's replay."""
+    with torch.cuda.stream(stream):
+        for _ in range(2):
+            fn()
+    stream.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=stream):
+        fn()
+    return g
+
+
+def _spoil_cached_workspaces():
+    """Fills every workspace that the helpers keep and checks later that nothing else wrote to it."""
+    torch.cuda.synchronize()
+    kept = list(cf._ws_cache.values())
+    cf._ws_cache.clear()
+    for ws in kept:
+        ws.fill_(0x5A)
+    return kept
+
+
+def test_captured_attention_keeps_no_cached_workspace():
+    """Keys split over workgroups need a workspace, which eager calls take from the helper's cache.  A graph outlives
+    what the cache holds (a larger call replaces it), so it must not refer to it: replays with the cached workspaces
+    overwritten are right and leave them as they are; a workspace of the caller's own is used."""
+    g = torch.Generator(device="cuda").manual_seed(8)
+    Q, K, V = (torch.randn((2, 8, n, 128), generator=g, device="cuda").bfloat16() for n in (1, 3000, 3000))
+    out = torch.empty_like(Q)
+    ref = cf.b2b_attention(Q, K, V)
+    stream = torch.cuda.Stream()
+    graph = _captured(lambda: cf.b2b_attention(Q, K, V, out=out), stream)
+    kept = _spoil_cached_workspaces()
+    for _ in range(4):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert float((out.float() - ref.float()).norm() / ref.float().norm()) < 5e-3
+        assert torch.equal(cf.b2b_attention(Q, K, V), ref)       # eager work between the replays
+    assert kept and all(bool((ws == 0x5A).all()) for ws in kept)
+    ws = torch.zeros(8 << 20, dtype=torch.uint8, device="cuda")
+    own = _captured(lambda: cf.b2b_attention(Q, K, V, out=out, ws=ws), stream)
+    for _ in range(3):
+        out.zero_()
+        own.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    assert int(ws[:cf.CF_B2B_WS_HEADER_BYTES].sum()) == 0 and int(ws.count_nonzero()) > 0
+
+
+def test_captured_narrow_row_call_keeps_no_cached_workspace():
+    """The same for row calls whose workspace is optional (check=False lets eager calls take it)."""
+    inp = I.postnorm_inputs(200, 400, 224, "bf16", seed=43)
+    args = _postnorm_operands(inp)
+    Y = torch.empty_like(args[3])
+    call = lambda **kw: cf.gemm_postnorm(*args, eps=inp.eps, out=Y, check=False, **kw)
+    ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, inp.gamma, inp.beta, 1.0, inp.eps)
+    stream = torch.cuda.Stream()
+    graph = _captured(call, stream)
+    kept = _spoil_cached_workspaces()
+    for _ in range(4):
+        Y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert_close_bf16(host(Y), ref, "replay")
+        call()
+        cf.check_workspace(cf.workspace(cf.CF_WS_OPTIONAL_BYTES, "cuda"))
+        assert_close_bf16(host(Y), ref, "eager between replays")
+    assert kept and all(bool((ws == 0x5A).all()) for ws in kept)
+    ws = torch.zeros(cf.CF_WS_OPTIONAL_BYTES, dtype=torch.uint8, device="cuda")
+    own = _captured(lambda: call(ws=ws), stream)
+    before = int(ws.count_nonzero())
+    for _ in range(3):
+        Y.zero_()
+        own.replay()
+        cf.check_workspace(ws)
+        assert_close_bf16(host(Y), ref, "the caller's workspace")
+    assert before > 0
