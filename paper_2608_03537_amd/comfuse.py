@@ -26,6 +26,7 @@ CF_LAYOUT_KN, CF_LAYOUT_NK = 0, 1
 CF_MID_GELU_BIAS, CF_MID_SOFTMAX, CF_MID_RELU_BIAS = 0, 1, 2
 CF_OUT_STORE, CF_OUT_BIAS_RESIDUAL_LN, CF_OUT_BIAS_RELU = 0, 1, 2
 PATH_AUTO, PATH_WHOLE_ROW, PATH_CLUSTER, PATH_SPLIT = 0, 1, 2, 3
+CF_WS_HEADER_BYTES = 8916992       # zero-filled start of a row workspace
 CF_WS_OPTIONAL_BYTES = 8917008     # a workspace query's answer where the workspace may be left out
 CF_B2B_WS_HEADER_BYTES = 1 << 20   # split-MLP arrival counters at the start of its workspace
 STATUS = {0: "CF_OK", 1: "CF_ERR_NULL", 2: "CF_ERR_SHAPE", 3: "CF_ERR_LD", 4: "CF_ERR_ALIGN",
@@ -200,23 +201,52 @@ def _stream(stream):
     return s.cuda_stream
 
 
-_ws_cache: dict = {}
+_ws_cache: dict = {}   # (device, stream, kind) -> workspace of eager calls
+_ws_graph: dict = {}   # the same -> (capture, workspace) of the last capture
 
 
 def _capturing():
     return _torch().cuda.is_current_stream_capturing()
 
 
+def _capture_id(stream):
+    """Number of the graph capture that ``stream`` takes part in, or None."""
+    status, number = C.c_int(), C.c_ulonglong()
+    e = lib().hipStreamGetCaptureInfo(C.c_void_p(_stream(stream)), C.byref(status), C.byref(number))
+    return number.value if e == 0 and status.value == 1 else None
+
+
+def _graph_workspace(nbytes, key, device, stream):
+    """The workspace of the capture in progress: allocated in it, so that the
+    graph owns the memory, and its header zero-filled by the graph's first
+    node that uses it, so that no replay depends on what ran before."""
+    torch = _torch()
+    capture = _capture_id(stream)
+    have = _ws_graph.get(key)
+    if have is None or capture is None or have[0] != capture or have[1].numel() < nbytes:
+        header = CF_WS_HEADER_BYTES if key[2] == "rows" else CF_B2B_WS_HEADER_BYTES
+        with torch.cuda.stream(stream):
+            ws = torch.empty(max(nbytes, header), dtype=torch.uint8, device=device)
+            ws[:header].view(torch.int32).zero_()
+        have = _ws_graph[key] = (capture, ws)
+    return have[1]
+
+
 def workspace(nbytes, device, stream=None, kind="rows"):
     """A zero-initialised workspace of at least nbytes on ``device``, cached per
     (device, stream, kind): calls on one stream run in order, so they may
     share it; calls on different streams get different workspaces (the
-    row-cluster round counters live in it).  kind "b2b" is the split MLP's
-    (its arrival counters must not meet another entry point's data)."""
+    row-cluster round counters live in it).  kind "b2b" is that of the split
+    MLP and of attention with split keys (their arrival counters must not meet
+    another entry point's data).  Calls captured into a graph share one of the
+    capture's own, never an eager one: a graph outlives what the cache holds,
+    and its replays may overlap eager calls or another graph."""
     torch = _torch()
     if nbytes == 0:
         return None
     key = (str(device), _stream(stream), kind)
+    if _capturing():
+        return _graph_workspace(nbytes, key, device, stream)
     ws = _ws_cache.get(key)
     if ws is None or ws.numel() < nbytes:
         # made on the stream that will use it, so the zero-fill runs before the call

@@ -198,3 +198,69 @@ def test_captured_narrow_row_call_keeps_no_cached_workspace():
         cf.check_workspace(ws)
         assert_close_bf16(host(Y), ref, "the caller's workspace")
     assert before > 0
+
+
+def _check_replays(graph, call, Y, check, kept=()):
+    """Replays of `graph` against the expected result, with eager work and fresh allocations between them."""
+    for i in range(4):
+        Y.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        check(f"replay {i}")
+        Y.zero_()
+        call()
+        torch.cuda.synchronize()
+        check(f"eager call after replay {i}")
+        torch.full((64 << 20,), 0x5A, dtype=torch.uint8, device="cuda")
+    assert all(bool((ws == 0x5A).all()) for ws in kept)
+
+
+@pytest.mark.parametrize("warm", [False, True])
+def test_captured_cluster_calls_own_their_workspace(warm):
+    """Row clusters captured into a graph without a workspace of the caller's own, with and without eager calls on
+    the stream before (a cold capture must not leave eager calls a buffer that only the graph's replay would zero):
+    replays are right with the helper's cached workspaces overwritten, eager calls before the first replay and between
+    replays too, and so is a second graph that is replayed first."""
+    inp = I.postnorm_inputs(300, 256, 768, "bf16", seed=44)
+    args = _postnorm_operands(inp)
+    Y = torch.empty_like(args[3])
+    call = lambda: cf.gemm_postnorm(*args, eps=inp.eps, out=Y, check=False)
+    ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, inp.gamma, inp.beta, 1.0, inp.eps)
+    check = lambda what: assert_close_bf16(host(Y), ref, what)
+    stream = torch.cuda.Stream()
+    if warm:
+        with torch.cuda.stream(stream):
+            call()
+        stream.synchronize()
+    graphs = []
+    for _ in range(2):
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=stream):
+            call()
+            call()
+        graphs.append(g)
+        # one buffer for both calls of the capture
+        capture, ws = cf._ws_graph[str(Y.device), stream.cuda_stream, "rows"]
+        assert capture is not None and ws.numel() == cf.CF_WS_HEADER_BYTES
+    kept = _spoil_cached_workspaces()
+    with torch.cuda.stream(stream):
+        Y.zero_()
+        call()
+        cf.check_workspace(cf.workspace(cf.CF_WS_HEADER_BYTES, "cuda"))
+    check("eager call before the first replay")
+    _check_replays(graphs[1], call, Y, check)
+    _check_replays(graphs[0], call, Y, check, kept)
+
+
+def test_captured_split_mlp_owns_its_workspace():
+    """The same for the split MLP, whose arrival counters must be zero."""
+    inp = I.dlrm_mlp_inputs(M=4200, K=1088)
+    X, W1, W2 = dev(inp.X), dev(np.ascontiguousarray(inp.W1.T)), dev(np.ascontiguousarray(inp.W2.T))
+    b1, b2 = dev(inp.b1, "f32"), dev(inp.b2, "f32")
+    Y = torch.empty((inp.M, 128), dtype=torch.bfloat16, device="cuda")
+    call = lambda: cf.b2b_mlp(X, W1, b1, W2, b2, out=Y)
+    ref = O.mlp_b2b(inp.X, inp.W1, inp.b1, inp.W2, inp.b2)
+    graph = _captured(call, torch.cuda.Stream())
+    kept = _spoil_cached_workspaces()
+    assert kept
+    _check_replays(graph, call, Y, lambda what: assert_close_bf16(host(Y), ref, what), kept)
