@@ -239,9 +239,10 @@ int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop,
 // Chooses kernel and row path for a GEMM (+ row subgraph).  `epi` selects the
 // epilogue: 0 = plain (alpha, bias, store), 1 = row subgraph.  `need_rows` is
 // true when the subgraph has a row reduction (then rows must be completed
-// across tiles); without one any tiling is valid.
+// across tiles); without one any tiling is valid.  few_rows = false leaves out
+// the tiles for few rows and the row clusters of an optional workspace.
 cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int path, int epi, bool need_rows,
-                    Plan& pl, bool allow_cluster = true, int64_t batch = 1, bool use_optional = true) {
+                    Plan& pl, bool allow_cluster = true, int64_t batch = 1, bool few_rows = true) {
   pl = Plan();
   if (!allow_cluster && need_rows) {
     if (path == PATH_CLUSTER)
@@ -317,9 +318,10 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
                          M > 32 * kAssumedCUs;
     // Fewer rows than fill the chip with 128-row tiles: 64 x 128 or small tiles,
     // as a row cluster or (row pass and second launch: about 4 us) small ones as
-    // the plain product of the split path.  Only where the automatic choice already
-    // takes a workspace, and not under an explicit path.
-    if (automatic && pl.kidx >= 0 && pl.mode == ROWS_LOCAL && use_optional && !several) {
+    // the plain product of the split path.  Not under an explicit path.  Where the
+    // choice so far takes no workspace, the cluster's is optional.
+    if (!automatic || !few_rows) {
+    } else if (pl.kidx >= 0 && pl.mode == ROWS_LOCAL && !several) {
       // Whole rows of 32 x TN on few CUs, or wide ones in many rounds: row
       // clusters if the caller gives a workspace and they are clearly faster.
       const double now = 0.85 * cost_whole(gemm_kernel(pl.kidx), M, K);
@@ -332,7 +334,7 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
         pl.mode = ROWS_CLUSTER;
         pl.optional = true;
       }
-    } else if (automatic && pl.kidx >= 0 && pl.mode != ROWS_LOCAL) {
+    } else if (pl.kidx >= 0 && pl.mode != ROWS_LOCAL) {
       const double now = cost_128(pl.kidx, M, N, K, 1, pl.mode == ROWS_CLUSTER);
       const int sc = !allow_cluster ? -1 : pick_small(M, N, K, in_f32, w_nk, loop, 1, true,
                                                       pl.mode == ROWS_SPLIT ? now + 4.0 : now);
@@ -608,8 +610,17 @@ cf_status rows_common(int64_t M, int64_t N, int64_t K, cf_dtype in, const void* 
     if (ws_bytes < pl.ws) return fail(CF_ERR_WORKSPACE, "workspace %zu < %zu bytes", ws_bytes, pl.ws);
     if (!aligned16(ws)) return fail(CF_ERR_ALIGN, "workspace is not 16-byte aligned");
   }
-  if (M == 0) return CF_OK;
-  if ((s = cap_slots(pl)) != CF_OK) return s;
+  if ((s = cap_slots(pl)) != CF_OK) {
+    // Too few co-resident workgroups for the peers of an automatic choice: the
+    // plan without it, where the workspace holds that.
+    Plan base;
+    if (path != PATH_AUTO ||
+        plan_rows(M, N, K, in == CF_F32, wl == CF_LAYOUT_NK, path, epi_kind, need_rows, base, !scratch, 1, false) !=
+            CF_OK ||
+        base.ws > (ws ? ws_bytes : 0) || cap_slots(base) != CF_OK)
+      return s;
+    pl = base;
+  }
   GemmRowsParams p{};
   p.batch = 1;
   p.M = (int)M;

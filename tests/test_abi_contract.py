@@ -248,3 +248,22 @@ def test_mlp_workspace_and_validation():
     assert cf.STATUS[cf.cf_b2bgemm(_mlp(K=96), A, 1 << 30, None)] == "CF_ERR_UNSUPPORTED"
     assert cf.STATUS[cf.cf_b2bgemm(_mlp(out=cf.CF_OUT_BIAS_RESIDUAL_LN), A, 1 << 30, None)] == "CF_ERR_UNSUPPORTED"
     assert cf.cf_b2bgemm(_mlp(M=0), None, 0, None) == 0
+
+
+def _no_device():
+    n = C.c_int(0)
+    return cf.lib().hipGetDeviceCount(C.byref(n)) != 0 or n.value == 0
+
+
+@pytest.mark.skipif(not _no_device(), reason="the addresses are fake: without a device nothing is launched")
+@pytest.mark.parametrize("M,N,K", [(200, 224, 400), (600, 256, 272), (9000, 768, 768)])
+def test_optional_workspace_never_refuses(M, N, K):
+    """A call whose workspace is optional runs on whole rows where the row cluster does not fit the device (here: no
+    device at all, so the launch fails, as it does without the workspace)."""
+    kw = dict(M=M, N=N, K=K, ldy=N, ldr=N, ldw=K, ldx=K)
+    need = cf.cf_gemm_postnorm_workspace(_pn(**kw))
+    assert need == cf.CF_WS_OPTIONAL_BYTES
+    assert cf.STATUS[_call(_pn(**kw))] == "CF_ERR_HIP"
+    assert cf.STATUS[_call(_pn(**kw), 0x7F0000800000, need)] == "CF_ERR_HIP", cf.cf_last_error()
+    # a path asked for by name is refused as before
+    assert cf.STATUS[_call(_pn(**dict(kw, N=768, ldy=768, ldr=768, path=2)), 0x7F0000800000, need)] == "CF_ERR_UNSUPPORTED"
