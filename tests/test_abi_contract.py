@@ -250,16 +250,13 @@ def test_mlp_workspace_and_validation():
     assert cf.cf_b2bgemm(_mlp(M=0), None, 0, None) == 0
 
 
-def _no_device():
-    n = C.c_int(0)
-    return cf.lib().hipGetDeviceCount(C.byref(n)) != 0 or n.value == 0
-
-
-@pytest.mark.skipif(not _no_device(), reason="the addresses are fake: without a device nothing is launched")
 @pytest.mark.parametrize("M,N,K", [(200, 224, 400), (600, 256, 272), (9000, 768, 768)])
 def test_optional_workspace_never_refuses(M, N, K):
     """A call whose workspace is optional runs on whole rows where the row cluster does not fit the device (here: no
     device at all, so the launch fails, as it does without the workspace)."""
+    torch = pytest.importorskip("torch")
+    if torch.cuda.is_available():
+        pytest.skip("the addresses are fake: only without a device is nothing launched")
     kw = dict(M=M, N=N, K=K, ldy=N, ldr=N, ldw=K, ldx=K)
     need = cf.cf_gemm_postnorm_workspace(_pn(**kw))
     assert need == cf.CF_WS_OPTIONAL_BYTES
