@@ -81,9 +81,14 @@ cf_status hip_status(hipError_t e, const char* what) {
 enum Path { PATH_AUTO = 0, PATH_WHOLE_ROW = 1, PATH_CLUSTER = 2, PATH_SPLIT = 3 };
 
 constexpr int kWholeRowMaxN = 768;
-constexpr int kClusterMaxPeers = 16;
+// An incomplete group of peers holds its CUs while it waits, and one call has at
+// most one such group on an XCD: with at most 16 peers two overlapping calls (on
+// two streams) leave an XCD's 32 CUs room to complete one of theirs, with
+// kAutoClusterPeers four do.  (Small tiles with one peer per CU of the XCD were
+// faster for a single stream, 16 x 1024 x 1024 8.5 us against 9.1, and two such
+// calls could starve each other.)
+constexpr int kClusterMaxPeers = kClusterPeers;
 constexpr int kAutoClusterPeers = 8;
-constexpr int kSmallMaxPeers = 32;   // small tiles: one per CU of an XCD
 
 struct Plan {
   int kidx = -1, mode = ROWS_LOCAL, cn = 1, num_rb = 0, slots = 0, tm = 0, tn = 0;
@@ -205,7 +210,7 @@ double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch, bool cl
 // The kernel of least cost among the small tiles (32 x 32, 32 x 64, 64 x 64) and,
 // for row clusters on the direct-to-LDS ring (loop 1, 2), the 64 x 128 tile, if
 // that is below `limit`; else -1.  cluster: column tiles must divide N into at
-// most 32 (64 x 128: 16) peers, whose row blocks run in rounds of the groups
+// most kClusterMaxPeers peers, whose row blocks run in rounds of the groups
 // resident on an XCD (32 CUs).  Measured post-norms (us; 32 x 64 / 64 x 64 / 64 x
 // 128 / 128 x 128): 333 x 768 x 3072 14.1 / 17.8 / - / 26.9; 1024 x 1024 x 1024
 // 17.4 / 13.6 / 12.1 / 15.8; 2048 x 1024 x 1024 30 / 22.9 / 13.2 / 16.2; 1536 x
@@ -216,9 +221,8 @@ double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch, bool cl
 int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop, int64_t batch, bool cluster,
                double limit) {
   int best = -1;
-  struct { int tm, tn, loop, epi, peers; } const tiles[] = {
-      {32, 32, w_nk ? 1 : 2, 3, kSmallMaxPeers}, {32, 64, w_nk ? 1 : 2, 3, kSmallMaxPeers},
-      {64, 64, w_nk ? 1 : 2, 3, kSmallMaxPeers}, {64, 128, loop, 1, kClusterMaxPeers}};
+  struct { int tm, tn, loop, epi; } const tiles[] = {
+      {32, 32, w_nk ? 1 : 2, 3}, {32, 64, w_nk ? 1 : 2, 3}, {64, 64, w_nk ? 1 : 2, 3}, {64, 128, loop, 1}};
   for (const auto& t : tiles) {
     if (t.epi == 1 && (!cluster || loop < 1)) continue;
     const int idx = find_gemm_kernel(in_f32, t.tm, t.tn, t.loop, t.epi);
@@ -227,7 +231,7 @@ int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop,
     const int64_t wgs = rb * cn * batch;
     int64_t rounds = (wgs + kAssumedCUs - 1) / kAssumedCUs;
     if (cluster) {
-      if (N % t.tn != 0 || cn > t.peers || kArriveUnit % (unsigned long long)cn != 0) continue;
+      if (N % t.tn != 0 || cn > kClusterMaxPeers) continue;
       rounds = cluster_rounds(rb, cn);
     }
     const double c = plan_cost(gemm_kernel(idx), rounds, wgs, K, cluster);
@@ -359,7 +363,7 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
   // the finish pass reads a row's partials one per lane of a 64-lane wave
   if (pl.mode == ROWS_SPLIT && t.epi == 2 && pl.cn > 64)
     return fail(CF_ERR_UNSUPPORTED, "split path: %d tiles per row exceed 64", pl.cn);
-  if (pl.mode == ROWS_CLUSTER && (t.epi == 3 ? pl.tm * pl.cn > kRecRows * kRecPeers : pl.tm > kRecRows || pl.cn > kRecPeers))
+  if (pl.mode == ROWS_CLUSTER && (pl.tm > kRecRows || pl.cn > kClusterPeers))
     return fail(CF_ERR_UNSUPPORTED, "cluster path: tile of %d rows x %d peers exceeds the exchange records",
                 pl.tm, pl.cn);
   size_workspace(pl, M, N, allow_cluster);

@@ -19,9 +19,8 @@
 // its L2; see cluster_exchange for the protocol, which this kernel follows: one
 // add to the group's round counter per tile, records that carry the round,
 // bounded waits, the sticky error word).  A record's position here is peer x TM
-// + row within the slot's area, which up to 32 peers of 64 rows fit; positions of
-// different slots never meet, so any record in a slot's area carries a round
-// of that slot whatever tile wrote it.
+// + row within the slot's area; positions of different slots never meet, so any
+// record in a slot's area carries a round of that slot whatever tile wrote it.
 //
 // K need not fill whole stages: chunks past K are loaded from clamped addresses
 // and replaced by zeros in the fragments of the last stage.
@@ -51,7 +50,7 @@ struct Small {
   static_assert(NW * TM * PITCH <= NW * RING && LDS <= 160 * 1024, "LDS budget");
   static_assert(!KN || sizeof(T) == 2, "K x N: bf16");
   static_assert((PX + PW) * S < 64, "vmcnt range");
-  static_assert(32 * TM <= kRecPeers * kRecRows, "records of 32 peers");
+  static_assert(TM <= kRecRows, "records of kClusterPeers peers");
 };
 
 // The K x N form: fragments of one 32-column block by transposing reads, k
@@ -335,7 +334,7 @@ void gemm_small_kernel(GemmRowsParams p) {
     if (e.bias) each([&](float& v, int g, int q) { v += bs[g][q]; });
     if (e.R) each([&](float& v, int g, int q) { v += rs[g][q]; });
 
-    constexpr int PP = 32 / S::TPR;   // peers one lane reads
+    constexpr int PP = kClusterPeers / S::TPR;   // peers one lane reads
     const bool peers = cluster && p.cn > 1;
     const float invN = 1.0f / (float)N;
     int stage = 0;

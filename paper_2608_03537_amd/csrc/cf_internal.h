@@ -62,27 +62,25 @@ struct GemmRowsParams {
   int leader;                    // CLUSTER: leader-follower exchange (peer 0 merges and broadcasts)
 };
 
-// Each of the NW waves of the cn workgroups of a peer group adds
-// kArriveUnit / (cn * NW) to the group's counter once per tile, so a round
-// adds exactly kArriveUnit.  lcm(1..16) * 8 is divisible by cn * NW for every
-// cn <= 16 and NW in {1, 2, 4, 8}; groups of more peers (small tiles, up to 32)
-// are planned only where the count divides it.
+constexpr int kClusterPeers = 16;                    // most workgroups of a peer group
+// Each of the cn workgroups of a peer group adds kArriveUnit / cn to the group's
+// counter once per tile, so a round adds exactly kArriveUnit, a multiple of
+// lcm(1..16).
 constexpr unsigned long long kArriveUnit = 720720ull * 8ull;
 constexpr int kMaxSlots = 64;                        // concurrent peer groups
 // Exchange records: [stage 2][round parity 2][slot kMaxSlots][peer kRecPeers]
-// [row kRecRows] x 2 words (peer kRecLead: the leader's merged values; small tiles
-// put up to 32 peers of at most 64 rows into the same words of their slot).  A
-// record's position lies in its slot's words, whatever the launch's peer count:
-// round numbers grow per slot, so a
-// record left by an earlier call in a position only ever carries an older
-// round of the same slot (a position shared by different slots could hold
+// [row kRecRows] x 2 words (peer kRecLead: the leader's merged values; the small
+// tiles lay their peers' rows side by side in the same words).  A record's position
+// lies in its slot's words, whatever the launch's peer count: round numbers grow
+// per slot, so a record left by an earlier call in a position only ever carries an
+// older round of the same slot (a position shared by different slots could hold
 // another slot's equal round number).  The parity of the round selects one
 // of two record sets: a fast peer that has finished round r and publishes
 // round r + 1 writes the other set, so a slow peer still reading round r
 // never finds its value overwritten.  (It cannot get two rounds ahead: round
 // r + 1 completes only with every peer's round r + 1 record, written after
 // that peer finished round r.)
-constexpr int kRecPeers = 17, kRecRows = 128;        // peers 0..15, then the leader's broadcast
+constexpr int kRecPeers = kClusterPeers + 1, kRecRows = 128;   // the peers, then the leader's broadcast
 constexpr int kRecLead = 16;                         // record of the merged values (leader-follower)
 constexpr int kLeaderFollowerPeers = 16;             // peer counts from which the leader merges for all
 constexpr size_t kRecSetWords = (size_t)kMaxSlots * kRecPeers * kRecRows * 2;   // one parity of one stage

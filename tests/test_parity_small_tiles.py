@@ -1,6 +1,6 @@
 """GPU parity of the small tiles (32 x 32, 32 x 64, 64 x 64, split K inside the
 workgroup) that the automatic path takes for few rows, against the fp64 oracle:
-row clusters of up to 32 peers, the plain product of the split path, and plain
+row clusters of up to 16 peers, the plain product of the split path, and plain
 products, at the edges of tiles, of K stages and of the row count."""
 import numpy as np
 import pytest
@@ -51,7 +51,7 @@ def _chain(inp, layout, dtype, kind):
 @pytest.mark.parametrize("layout,dtype", [("nk", "bf16"), ("kn", "bf16"), ("nk", "f32")])
 @pytest.mark.parametrize("M,K,N", [
     (1, 512, 512),      # one row
-    (33, 1040, 1024),   # one row past a tile, K a quarter stage past whole stages, 32 or 16 peers
+    (33, 1040, 1024),   # one row past a tile, K a quarter stage past whole stages, 16 peers
     (65, 48, 768),      # less than one stage: three waves have no k
     (300, 272, 640),    # 32 x 64 tiles, an odd number of stages per wave
     (1000, 528, 768),   # 64 x 128 tiles (bf16 on the ring) or 64 x 64, ragged last row block
@@ -65,8 +65,8 @@ def test_row_clusters(M, K, N, layout, dtype, kind):
 
 
 @pytest.mark.parametrize("layout", ["nk", "kn"])
-@pytest.mark.parametrize("M,N", [(40, 1024),    # cluster of 32 or 16 peers, two exchanges
-                                 (129, 2048),   # cluster of 32 peers
+@pytest.mark.parametrize("M,N", [(40, 1024),    # cluster of 16 peers, two exchanges
+                                 (129, 2048),   # cluster of 16 peers
                                  (70, 4128)])   # split path: plain product with a ragged last column tile
 def test_quant_chain(M, N, layout):
     inp = I.postnorm_inputs(M, 1040, N, "bf16", seed=52, with_affine=False)
@@ -159,3 +159,41 @@ def test_optional_workspace(dtype, M, K, N):
         cf.check_workspace(ws)
         check(host(Y), ref, "row clusters")
     assert int(ws.sum()) != 0
+
+
+@pytest.mark.parametrize("dtype,M,K,N,rows", [
+    ("bf16", 16, 1024, 1024, 32), ("bf16", 64, 2048, 2048, 64), ("bf16", 33, 1040, 1024, 32), ("f32", 32, 640, 640, 32),
+    ("f32", 100, 512, 768, 32), ("bf16", 5, 272, 1280, 128)])
+def test_groups_leave_room_for_another_call(dtype, M, K, N, rows):
+    """An XCD has 32 CUs, and a waiting group holds one per peer: with at most 16 peers two overlapping calls always
+    complete.  The peers are counted by the records that a call on a fresh workspace leaves, `rows` from each."""
+    inp = I.postnorm_inputs(M, K, N, dtype, seed=56, with_affine=False)
+    ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
+    cf.gemm_postnorm(dev(inp.X, dtype), dev(I.lay_out_weight(inp.W, "nk"), dtype), dev(inp.bias, "f32"),
+                     dev(inp.R, dtype), eps=inp.eps, ws=ws, check=False)
+    cf.check_workspace(ws)
+    words = ws[4096:cf.CF_WS_HEADER_BYTES].view(torch.int64)
+    set_words, peer_words = 64 * 17 * 128 * 2, 128 * 2       # one parity of one stage; one peer of a slot
+    first = words[set_words:set_words + 16 * peer_words]     # round 1 is odd: second set; without the leader's record
+    peers = int(first.count_nonzero()) // 2 / rows
+    assert 1 < peers <= 16 and peers == int(peers), peers
+
+
+def test_two_streams_of_row_clusters():
+    """Calls with the largest groups on two streams at once, each with a workspace of its own, all on one XCD: all of
+    them complete and are right."""
+    inp = I.postnorm_inputs(16, 512, 1024, "bf16", seed=57, with_affine=False)
+    X, W, b, R = dev(inp.X), dev(I.lay_out_weight(inp.W, "nk")), dev(inp.bias, "f32"), dev(inp.R)
+    ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, None, None, 1.0, inp.eps)
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [[torch.empty_like(R) for _ in range(50)] for _ in streams]
+    torch.cuda.synchronize()
+    for i in range(50):
+        for s, out in zip(streams, outs):
+            with torch.cuda.stream(s):
+                cf.gemm_postnorm(X, W, b, R, eps=inp.eps, out=out[i], check=False)
+    torch.cuda.synchronize()
+    for s, out in zip(streams, outs):
+        cf.check_workspace(cf.workspace(cf.CF_WS_HEADER_BYTES, "cuda", s), s)
+        for y in out:
+            assert_close_bf16(host(y), ref, "overlapping calls")
