@@ -9,6 +9,8 @@ Attention: O = softmax(Q K^T / sqrt(d)) V per head, online softmax; rel-RMS
 5e-3 is the binding check (|O| is small, so max-abs 2e-2 is loose), plus the
 invariants V = 1 -> O = 1 and Q = 0 -> O = mean_j V_j.
 """
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -109,9 +111,6 @@ def run_attn(Q, K, V, scale=None):
     return host(o)
 
 
-# Ragged Lk puts the partial last key block in either ring stage: with an odd
-# block count (300, 289 keys) it is loaded from stage 1's step, with an even
-# one (333, 350) from stage 0's, for both head dimensions.
 @pytest.mark.parametrize("d,N1", [(64, 128), (128, 256), (256, 256), (256, 512)])
 @pytest.mark.parametrize("batch,M,own", [(1, 1, True), (1, 33, False), (2, 1000, True), (1, 8192, False),
                                          (1, 8193, True), (3, 2753, False)])
@@ -141,6 +140,15 @@ def test_ffn_forms(batch, M, own, d, N1):
     assert float((err.abs() / o.abs().clamp(min=1.0)).max()) < 2e-2
 
 
+def attention_form(M, batch, Lk, d):
+    """(query waves per workgroup, 0 for two workgroups per CU; workgroups that share a query block's keys): the
+    library's own choice, by its C++ name."""
+    f = cf.lib()._ZN2cf14attention_formEllli
+    f.argtypes, f.restype = (C.c_int64, C.c_int64, C.c_int64, C.c_int), C.c_uint64
+    r = f(M, batch, Lk, d)
+    return r & 0xFFFFFFFF, r >> 32
+
+
 @pytest.mark.parametrize("B,H,Lq,Lk,d", [(1, 2, 200, 300, 64), (2, 1, 129, 64, 128), (1, 3, 64, 1, 128),
                                          (1, 1, 256, 333, 128), (1, 2, 130, 289, 128), (1, 1, 100, 350, 64)])
 def test_attention_small(B, H, Lq, Lk, d):
@@ -149,6 +157,23 @@ def test_attention_small(B, H, Lq, Lk, d):
     ref = O.attention(a.Q, a.K, a.V)
     assert rel_rms(got, ref) < 5e-3, rel_rms(got, ref)
     assert max_abs(got, ref) < 2e-2
+
+
+# Ragged Lk puts the partial last key block in either ring stage: with an odd
+# block count (289 keys: five of 64) it is loaded from stage 1's step, with an
+# even one (333: six) from stage 0's, for both head dimensions.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("Lk", [289, 333, 33, 70])
+def test_attention_two_workgroups_per_cu(Lk, d):
+    """The form of large calls (four query waves, one key group) with a partial last key block, some heads against the
+    oracle."""
+    B, H, Lq = 1, 257, 70
+    assert attention_form(Lq, B * H, Lk, d) == (0, 1)
+    a = I.attention_inputs(seed=9, B=B, H=H, Lq=Lq, Lk=Lk, d=d)
+    got = run_attn(a.Q, a.K, a.V)
+    heads = [0, 1, 100, 255, 256]
+    ref = O.attention(a.Q[:, heads], a.K[:, heads], a.V[:, heads])
+    assert rel_rms(got[:, heads], ref) < 5e-3 and max_abs(got[:, heads], ref) < 2e-2
 
 
 @pytest.mark.parametrize("which", ["self", "target"])
@@ -191,21 +216,24 @@ def test_attention_full_size_sampled_rows():
 
 
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("B,H,Lq,Lk", [
-    (1, 3, 1, 1),        # one query, one key: three of four key groups empty
-    (2, 16, 5, 33),      # two key blocks, the last of one key
-    (1, 2, 31, 1000),    # few queries, keys split over workgroups, ragged last block
-    (2, 8, 16, 4097),    # the same, one key past a block
-    (1, 9, 33, 290),     # two 32-query blocks
-    (70, 4, 33, 129),    # 32 < Lq <= 64: two query waves, four key groups
-    (5, 13, 250, 200),   # 195 64-query blocks
-    (70, 4, 33, 128),    # the same with the most keys that keep one group
-    (4, 16, 511, 192),   # and for four query waves
-    (4, 16, 511, 321),   # 256 128-query blocks: two key groups, an odd number of key blocks
+@pytest.mark.parametrize("B,H,Lq,Lk,qg", [
+    (1, 3, 1, 1, 1),        # one query, one key: three of four key groups empty (d = 64: one key group)
+    (2, 16, 5, 33, 1),      # two key blocks, the last of one key
+    (1, 2, 31, 1000, 1),    # few queries, keys split over workgroups, ragged last block
+    (2, 8, 16, 4097, 1),    # the same, one key past a block
+    (1, 9, 33, 290, 1),     # two 32-query blocks
+    (70, 4, 33, 129, 2),    # 32 < Lq <= 64: two query waves, four key groups
+    (5, 13, 250, 200, 4),   # 130 128-query blocks: four query waves, two key groups
+    (70, 4, 33, 128, 0),    # two query waves, with the most keys that keep one group
+    (4, 16, 511, 192, 0),   # and for four query waves
+    (4, 16, 511, 321, 4),   # 256 128-query blocks: an odd number of key blocks
+    (1, 16, 600, 321, 2),   # 160 64-query blocks
 ])
-def test_attention_key_groups(B, H, Lq, Lk, d):
+def test_attention_key_groups(B, H, Lq, Lk, qg, d):
     """Shapes that take a form with several key groups per workgroup (and, with few queries, several workgroups per
     query block), with the workspace and without it, against the oracle on some heads."""
+    form = attention_form(Lq, B * H, Lk, d)
+    assert form[0] == (0 if d == 64 and Lk <= 64 else qg) and (form[1] > 1) == (Lk >= 1000)
     g = torch.Generator(device="cuda").manual_seed(Lq + Lk)
     Q, K, V = (torch.randn((B, H, n, d), generator=g, device="cuda").bfloat16() for n in (Lq, Lk, Lk))
     got = [cf.b2b_attention(Q, K, V), cf.b2b_attention(Q, K, V)]
@@ -244,3 +272,74 @@ def test_attention_minus_infinity_scores_in_whole_key_groups():
         sc[::2, 20:] = float("-inf")
         ref = torch.softmax(sc, 1) @ V[0, h].double()
         assert float((got[0, h].double() - ref).abs().max()) < 2e-2
+
+
+def _wide(g, *shape, std=1.0, pad=8, gap=24):
+    """A bf16 tensor whose rows lie `pad` elements apart and whose matrices `gap` further; NaN in between."""
+    *lead, rows, cols = shape
+    n = int(np.prod(lead)) if lead else 1
+    sb = rows * (cols + pad) + gap
+    store = torch.full((n * sb,), float("nan"), device="cuda", dtype=torch.bfloat16)
+    t = store.as_strided((n, rows, cols), (sb, cols + pad, 1))
+    t.copy_(torch.randn((n, rows, cols), generator=g, device="cuda") * std)
+    return t, sb, cols + pad
+
+
+@pytest.mark.parametrize("B,Lq,Lk,d", [(16, 1, 2111, 128), (8, 3, 1000, 64), (40, 40, 333, 64), (130, 40, 333, 128),
+                                       (60, 400, 333, 64), (60, 400, 289, 128), (257, 70, 289, 64), (257, 70, 333, 128)])
+def test_attention_row_pitches_and_batch_strides(B, Lq, Lk, d):
+    """Every form with row pitches beyond d and gaps between the heads (the Python helper takes contiguous ones only),
+    against an fp64 softmax; what lies between the rows is neither read into a result nor written."""
+    g = torch.Generator(device="cuda").manual_seed(B + Lk)
+    (Q, sq, lq), (K, sk, lk), (V, sv, lv) = (_wide(g, B, n, d) for n in (Lq, Lk, Lk))
+    out = torch.full((B, Lq, d + 16), 7.0, device="cuda", dtype=torch.bfloat16)
+    a = cf._b2b_args(batch=B, M=Lq, K=d, N1=Lk, N2=d, dtype=cf.CF_BF16, X=Q.data_ptr(), ldx=lq, sx=sq, W1=K.data_ptr(),
+                     ldw1=lk, sw1=sk, w1_layout=cf.CF_LAYOUT_NK, mid=cf.CF_MID_SOFTMAX, mid_scale=d ** -0.5,
+                     W2=V.data_ptr(), ldw2=lv, sw2=sv, w2_layout=cf.CF_LAYOUT_KN, out=cf.CF_OUT_STORE, O=out.data_ptr(),
+                     ldo=d + 16, so=Lq * (d + 16))
+    need = cf.cf_b2bgemm_workspace(a)
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda") if need else None
+    for w in {None, ws}:
+        out[..., :d] = 0.0
+        cf._check(cf.cf_b2bgemm(a, cf._ptr(w), 0 if w is None else w.numel(), torch.cuda.current_stream().cuda_stream))
+        torch.cuda.synchronize()
+        for h in (0, B // 2, B - 1):
+            ref = torch.softmax(Q[h].double() @ K[h].double().t().contiguous() * d ** -0.5, 1) @ V[h].double()
+            err = out[h, :, :d].double() - ref
+            assert float(err.norm() / ref.norm()) < 5e-3 and float(err.abs().max()) < 2e-2
+        assert bool((out[..., d:] == 7.0).all()) and bool(torch.isfinite(out).all())
+
+
+@pytest.mark.parametrize("M", [70, 3000])
+@pytest.mark.parametrize("d,N1", [(64, 128), (256, 512)])
+def test_ffn_row_pitches_and_special_values(d, N1, M):
+    """Both FFN forms (32-row and, with 3 x 3000 rows, 128-row workgroups) with row pitches beyond the row and gaps
+    between the batch entries; then rows of X that hold an infinity or NaN: they become NaN (LayerNorm) and no other
+    row changes a bit."""
+    g = torch.Generator(device="cuda").manual_seed(M + d)
+    (X, sx, lx), (W1, sw1, l1), (W2, sw2, l2) = (_wide(g, 3, *s, std=f) for s, f in (
+        ((M, d), 1.0), ((N1, d), d ** -0.5), ((d, N1), N1 ** -0.5)))
+    R, _, _ = _wide(g, 3, M, d)
+    b1, b2, gamma = (torch.randn(n, generator=g, device="cuda") * 0.5 for n in (N1, d, d))
+    out = torch.full((3, M, d + 8), 7.0, device="cuda", dtype=torch.bfloat16)
+    cf.b2b_ffn(X, W1, b1, W2, b2, R, gamma, out=out[..., :d])
+    torch.cuda.synchronize()
+    for i in range(3):
+        h = X[i].double() @ W1[i].double().t().contiguous() + b1.double()
+        o = (0.5 * h * (1.0 + torch.erf(h / 2 ** 0.5))) @ W2[i].double().t().contiguous() + b2.double() + R[i].double()
+        o = o - o.mean(1, keepdim=True)
+        o = o / torch.sqrt(o.square().mean(1, keepdim=True) + 1e-5) * gamma.double()
+        err = out[i, :, :d].double() - o
+        assert float(err.norm() / o.norm()) < 5e-3 and float((err.abs() / o.abs().clamp(min=1.0)).max()) < 2e-2
+    assert bool((out[..., d:] == 7.0).all())
+    before = out[..., :d].clone()
+    spoiled = [(0, 3, 5, float("inf")), (1, 40, 0, float("nan")), (2, M - 1, d - 1, float("-inf"))]
+    for b, m, k, v in spoiled:
+        X[b, m, k] = v
+    cf.b2b_ffn(X, W1, b1, W2, b2, R, gamma, out=out[..., :d])
+    torch.cuda.synchronize()
+    hit = torch.zeros((3, M), dtype=torch.bool, device="cuda")
+    for b, m, _, _ in spoiled:
+        hit[b, m] = True
+    assert bool(torch.isnan(out[..., :d][hit]).all())
+    assert torch.equal(out[..., :d][~hit], before[~hit])

@@ -137,3 +137,62 @@ def test_split_path_large_tile():
     assert float((Z[rows].double() - z).abs().max()) < 2e-2
     assert torch.allclose(s[rows].double(), z.abs().amax(1) / 448.0, rtol=1e-3)
     assert bool((Q.view(torch.uint8) & 0x7F).amax(1).eq(0x7E).all())     # the row maximum is coded as +-448
+
+
+def _apart(g, *shape, std=1.0, pad=8, gap=16, dtype=torch.bfloat16):
+    """A tensor whose rows lie `pad` elements apart and whose matrices `gap` further; NaN in between."""
+    *lead, rows, cols = shape
+    n = int(np.prod(lead)) if lead else 1
+    sb = rows * (cols + pad) + gap
+    store = torch.full((n * sb,), float("nan"), device="cuda", dtype=dtype)
+    t = store.as_strided((n, rows, cols), (sb, cols + pad, 1))
+    t.copy_(torch.randn((n, rows, cols), generator=g, device="cuda") * std)
+    return t if lead else t[0]
+
+
+PITCHED = [
+    (3, 33, 96, 272, "bf16"),       # 32 x 32 and 32 x 64 tiles, K past whole stages
+    (2, 17, 160, 1040, "f32"),
+    (1, 130, 4096, 1024, "bf16"),   # 64 x 64 tiles
+    (1, 2049, 4128, 1088, "bf16"),  # 256 x 256 tiles, one row and 32 columns past
+    (3, 2049, 2048, 1152, "bf16"),
+    (1, 300, 768, 784, "f32"),
+]
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("batch,M,N,K,dtype", PITCHED)
+def test_products_with_pitches_and_special_values(batch, M, N, K, dtype, layout):
+    """Row pitches beyond the row and gaps between batch entries, fp32 outputs against an fp32 product (see
+    test_gemm_large_tile for the bound; fp32 operands add their own rounding, 1e-4 as elsewhere); what lies between the
+    rows stays.  Then an infinity or NaN in the first, a middle and the last row of A (in the last k) and in the last
+    column of B: exactly their rows and columns are affected, as in the reference product."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+    A = _apart(g, batch, M, K, dtype=t)
+    B = _apart(g, batch, *((K, N) if layout == "kn" else (N, K)), std=K ** -0.5, dtype=t)
+    bias = torch.randn((N,), generator=g, device="cuda")
+    out = torch.full((batch, M, N + 8), 7.0, device="cuda")
+
+    def run():
+        cf.gemm(A, B, b_layout=cf.CF_LAYOUT_KN if layout == "kn" else cf.CF_LAYOUT_NK, bias=bias, alpha=0.5,
+                out=out[..., :N])
+        torch.cuda.synchronize()
+        ref = [0.5 * (A[b].float() @ (B[b].float() if layout == "kn" else B[b].float().t().contiguous())) + bias
+               for b in range(batch)]
+        return out[..., :N], torch.stack(ref)
+    got, ref = run()
+    assert float((got - ref).abs().max()) < (1e-4 if dtype == "f32" else 1e-5)
+    assert bool((out[..., N:] == 7.0).all())
+    clean = got.clone()
+    A[0, 0, K - 1], A[0, M // 2, 3], A[batch - 1, M - 1, K - 1] = float("inf"), float("nan"), float("-inf")
+    if layout == "kn":
+        B[0, K - 1, N - 1] = float("nan")
+    else:
+        B[0, N - 1, K - 1] = float("nan")
+    got, ref = run()
+    assert torch.equal(torch.isnan(got), torch.isnan(ref))
+    inf = torch.isinf(ref)
+    assert torch.equal(torch.isinf(got), inf) and torch.equal(got[inf], ref[inf])
+    same = torch.isfinite(ref)
+    assert torch.equal(got[same], clean[same])

@@ -197,3 +197,56 @@ def test_two_streams_of_row_clusters():
         cf.check_workspace(cf.workspace(cf.CF_WS_HEADER_BYTES, "cuda", s), s)
         for y in out:
             assert_close_bf16(host(y), ref, "overlapping calls")
+
+
+@pytest.mark.parametrize("layout", ["nk", "kn"])
+@pytest.mark.parametrize("dtype,M,K,N", [
+    ("bf16", 70, 272, 256),      # 32 x 32 tiles, K past whole stages
+    ("bf16", 333, 512, 768),     # 32 x 64
+    ("bf16", 999, 1040, 1024),   # 64 x 64
+    ("bf16", 1000, 512, 1024),   # 64 x 128 on the ring
+    ("bf16", 4097, 512, 2080),   # 256 x 256 tiles and a row pass, ragged
+    ("f32", 100, 272, 512),
+])
+def test_row_clusters_with_pitches_and_special_values(dtype, M, K, N, layout):
+    """Row pitches beyond the row for X, W, the residual, the stored rows and the codes; then an infinity or NaN in some
+    rows of X: those rows become NaN (LayerNorm), every other keeps its bits."""
+    g = torch.Generator(device="cuda").manual_seed(M + N + K)
+    t = torch.float32 if dtype == "f32" else torch.bfloat16
+
+    def apart(rows, cols, std=1.0, pad=16):
+        store = torch.full((rows, cols + pad), float("nan"), device="cuda", dtype=t)
+        store[:, :cols] = (torch.randn((rows, cols), generator=g, device="cuda") * std).to(t)
+        return store[:, :cols]
+    X, R = apart(M, K), apart(M, N)
+    W = apart(*((N, K) if layout == "nk" else (K, N)), std=K ** -0.5)
+    b = torch.randn(N, generator=g, device="cuda")
+    Z = torch.full((M, N + 8), 7.0, device="cuda")
+    s, Q = torch.zeros(M, device="cuda"), torch.full((M, N + 16), 7, device="cuda", dtype=torch.uint8)
+    spec = [dict(kind=cf.CF_N_BIAS, v0=b), dict(kind=cf.CF_N_RESIDUAL, ld=N + 16, dtype=cf._dt(R), **{"in": R}),
+            dict(kind=cf.CF_N_LAYERNORM, f0=1e-5), dict(kind=cf.CF_N_GELU),
+            dict(kind=cf.CF_N_STORE, out=Z, ld=N + 8, dtype=cf.CF_F32),
+            dict(kind=cf.CF_N_ROWAMAX_QUANT, out=s, out2=Q, ld=N + 16, f0=448.0)]
+    ws = torch.zeros(128 << 20, dtype=torch.uint8, device="cuda")
+
+    def run():
+        cf.gemm_subgraph(X, W, spec, w_layout=LAYOUT[layout], ws=ws, check=False)
+        cf.check_workspace(ws)
+        assert bool((Z[:, N:] == 7.0).all()) and bool((Q[:, N:] == 7).all())
+        return Z[:, :N].clone(), s.clone(), Q[:, :N].clone()
+    z, sc, q = run()
+    x = X.double() @ (W.double().t().contiguous() if layout == "nk" else W.double()) + b.double() + R.double()
+    x = x - x.mean(1, keepdim=True)
+    x = x / torch.sqrt(x.square().mean(1, keepdim=True) + 1e-5)
+    ref = 0.5 * x * (1.0 + torch.erf(x / 2 ** 0.5))
+    assert float((z.double() - ref).abs().max()) < 1e-4
+    s32, q32 = O.rowamax_quant_f32(z.cpu().numpy())
+    assert np.array_equal(sc.cpu().numpy(), s32) and np.array_equal(q.cpu().numpy(), q32)
+    rows = [0, M // 2, M - 1]
+    for m, k, v in zip(rows, (K - 1, 0, 5), (float("inf"), float("nan"), float("-inf"))):
+        X[m, k] = v
+    z2, sc2, q2 = run()
+    keep = torch.ones(M, dtype=torch.bool, device="cuda")
+    keep[rows] = False
+    assert bool(torch.isnan(z2[~keep]).all())
+    assert torch.equal(z2[keep], z[keep]) and torch.equal(sc2[keep], sc[keep]) and torch.equal(q2[keep], q[keep])
