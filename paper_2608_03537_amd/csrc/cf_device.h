@@ -187,21 +187,12 @@ __device__ __forceinline__ float tanh_exp(float z) {
   return copysignf((1.0f - t) * __builtin_amdgcn_rcpf(1.0f + t), z);
 }
 
-// exp(x - mx) = exp2(fma(x, sc, sh)) for the values x <= mx of a row, or of the part of one that a
-// tile holds.  mx is the part's maximum, raised to the lowest finite value first: the terms of a
-// part that is -infinity throughout are then 0 (they were NaN, here and in the merge of the parts).
-// Beyond 2.36e38 (masks of the type's lowest value) mx log2(e) overflows; values that large differ by
-// 2^103 at least where they differ, so any scale gives the same zeros and ones, and a power of two
-// leaves exactly 0 of x - mx at x = mx.
+// -max log2(e) of a row, or of the part of one that a tile holds, for exp(x - max) =
+// exp2(fma(x, log2(e), -max log2(e))): kept finite where the part is masked throughout, by -infinity
+// or by the type's lowest value.  Its terms and its sum are then 0 (they were NaN, which the merge
+// of the parts spread over the row); its maximum goes into the merge raised to the lowest value.
 constexpr float kLowestF32 = -3.4028234663852886e38f;
-struct SoftmaxExp {
-  float sc, sh;
-  __device__ __forceinline__ explicit SoftmaxExp(float mx) {
-    sc = fabsf(mx) > 2e38f ? 0.25f : 1.4426950408889634f;
-    sh = -mx * sc;
-  }
-  __device__ __forceinline__ float operator()(float x) const { return __builtin_amdgcn_exp2f(fmaf(x, sc, sh)); }
-};
+__device__ __forceinline__ float softmax_shift(float mx) { return fminf(-mx * 1.4426950408889634f, -kLowestF32); }
 
 __device__ __forceinline__ void store4(void* base, int64_t off, int f32, const float (&v)[4]) {
   if (f32) {

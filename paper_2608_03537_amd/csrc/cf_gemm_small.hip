@@ -8,7 +8,7 @@
 // Split K inside the workgroup.  A tile this small has too little work per k
 // step for waves to share, so each of the four waves computes the whole tile
 // over every fourth 128-byte k stage, with a ring of S stages of its own in
-// LDS: no barrier in the main loop, and S stages per wave (96 to 144 KB per
+// LDS: no barrier in the main loop, and S stages per wave (128 or 144 KB per
 // workgroup) in flight to cover the memory latency.  The four partial tiles are
 // added through LDS in wave order.
 //
@@ -18,7 +18,8 @@
 // workgroups of a row block share an XCD and exchange tagged records through
 // its L2; see cluster_exchange for the protocol, which this kernel follows: one
 // add to the group's round counter per tile, records that carry the round,
-// bounded waits, the sticky error word).  A record's position here is peer x TM
+// bounded waits, the sticky error word; only the add goes out in front of the main
+// loop here, whose first wait then covers it).  A record's position here is peer x TM
 // + row within the slot's area; positions of different slots never meet, so any
 // record in a slot's area carries a round of that slot whatever tile wrote it.
 //
@@ -415,10 +416,10 @@ void gemm_small_kernel(GemmRowsParams p) {
       float mx = -INFINITY;
       each([&](float& v, int g, int) { mx = val[g] ? fmaxf(mx, v) : mx; });
       mx = fmaxf(row_max<S::TPR>(mx), kLowestF32);
-      const SoftmaxExp ex(mx);
+      const float nl = softmax_shift(mx);
       float t = 0.0f;
       each([&](float& v, int g, int) {
-        v = val[g] ? ex(v) : 0.0f;
+        v = val[g] ? __builtin_amdgcn_exp2f(fmaf(v, 1.4426950408889634f, nl)) : 0.0f;
         t += v;
       });
       float sm = row_sum<S::TPR>(t), f = 1.0f;

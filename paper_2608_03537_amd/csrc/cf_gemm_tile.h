@@ -657,7 +657,8 @@ __device__ __forceinline__ void wg_stat_reduce(float (&n)[S::BM], float (&mean)[
 // group's counter once per tile (round_begin), so a round adds exactly
 // kArriveUnit and old / kArriveUnit numbers the round, identically in every
 // workgroup of the group.  The add goes out after the main loop (the loop's
-// waits count memory operations in issue order); the adding wave waits for
+// waits count memory operations in issue order; the small tiles' kernel adds in
+// front of it); the adding wave waits for
 // its return and leaves the round number in LDS before the workgroup's first
 // epilogue barrier (the other waves read it after that barrier).  So all adds
 // of a round have landed before any record of the round can be seen, and the
@@ -1342,8 +1343,7 @@ __device__ __forceinline__ void epilogue(f32x16_t (&x)[S::BM][S::BN], const EpiP
     wg_row_reduce<S, true>(mx, red, lane, wm, wn);
 #pragma unroll
     for (int bm = 0; bm < S::BM; ++bm) {
-      mx[bm] = fmaxf(mx[bm], kLowestF32);
-      const SoftmaxExp ex(mx[bm]);
+      const float nl = softmax_shift(mx[bm]);
       float t = 0.0f;
 #pragma unroll
       for (int bn = 0; bn < S::BN; ++bn)
@@ -1352,7 +1352,7 @@ __device__ __forceinline__ void epilogue(f32x16_t (&x)[S::BM][S::BN], const EpiP
           const bool v = full_n || ncol(bn, g) < N;
 #pragma unroll
           for (int q = 0; q < 4; ++q) {
-            const float ev = v ? ex(x[bm][bn][4 * g + q]) : 0.0f;
+            const float ev = v ? __builtin_amdgcn_exp2f(fmaf(x[bm][bn][4 * g + q], 1.4426950408889634f, nl)) : 0.0f;
             x[bm][bn][4 * g + q] = ev;
             t += ev;
           }
@@ -1364,7 +1364,7 @@ __device__ __forceinline__ void epilogue(f32x16_t (&x)[S::BM][S::BN], const EpiP
     if (p.mode == ROWS_CLUSTER && p.cn > 1) {
       float mg[S::BM];
 #pragma unroll
-      for (int bm = 0; bm < S::BM; ++bm) mg[bm] = mx[bm];
+      for (int bm = 0; bm < S::BM; ++bm) mg[bm] = mx[bm] = fmaxf(mx[bm], kLowestF32);
       cluster_exchange<S, MERGE_SOFTMAX>(p, 0, slot, c, tag(), mg, sm, lane, wm, wn);
       exchanged = true;
 #pragma unroll

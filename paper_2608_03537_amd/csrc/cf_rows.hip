@@ -209,14 +209,14 @@ __global__ __launch_bounds__(256) void row_kernel(RowKernelParams p) {
       if (val[j])
 #pragma unroll
         for (int q = 0; q < 4; ++q) mx = fmaxf(mx, v[j][q]);
-    mx = fmaxf(wave_max(mx), kLowestF32);
-    const SoftmaxExp ex(mx);
+    mx = wave_max(mx);
+    const float nl = -mx * 1.4426950408889634f;
     float s = 0.0f;
 #pragma unroll
     for (int j = 0; j < VPL; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const float t = val[j] ? ex(v[j][q]) : 0.0f;
+        const float t = val[j] ? __builtin_amdgcn_exp2f(fmaf(v[j][q], 1.4426950408889634f, nl)) : 0.0f;
         v[j][q] = t;
         s += t;
       }
