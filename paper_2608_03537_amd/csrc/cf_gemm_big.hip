@@ -19,18 +19,19 @@
 // loaded in the order in which they are read, one per phase, seven phases
 // ahead (up to 112 KB in flight).
 //
-// Ping-pong.  Every wave alternates a read section (two direct-to-LDS loads of
-// 1 KB, the LDS reads of the phase's piece, and the waits) with an MFMA section
-// (8 MFMAs, 256 cycles of the SIMD's matrix core), a barrier after each.  Waves
-// 4..7 run one section behind waves 0..3, and waves w and w + 4 share a SIMD,
-// so one of the two always issues MFMAs while the other reads.
+// Ping-pong.  Every wave alternates a read section (the LDS reads of the phase's
+// piece, and the waits) with an MFMA section (8 MFMAs, 256 cycles of the SIMD's
+// matrix core, and two direct-to-LDS loads of 1 KB between them: in the read
+// section the loads held up the LDS reads behind them), a barrier after each.
+// Waves 4..7 run one section behind waves 0..3, and waves w and w + 4 share a
+// SIMD, so one of the two always issues MFMAs while the other reads.
 //
-// Waits.  In phase p (counted over all steps) a wave issues piece p + 8 and
-// reads piece p + 1 (piece 0 is read before the loop).  Before the barrier that
-// ends its read section it waits for its own share of piece p + 2, which leaves
-// at most the pieces p + 3 .. p + 8 (two loads each) outstanding.  Waves 4..7
-// do the same one section later, still before the barrier in front of the read
-// section in which waves 0..3 read that piece.  A piece read in phase p has
+// Waits.  In phase p (counted over all steps) a wave reads piece p + 1 (piece 0
+// is read before the loop) and then, with its MFMAs, issues piece p + 8.  Before
+// the barrier that ends its read section it waits for its own share of piece
+// p + 2, which leaves at most the pieces p + 3 .. p + 7 (two loads each)
+// outstanding.  Waves 4..7 do the same one section later, still before the
+// barrier in front of the read section in which waves 0..3 read that piece.  A piece read in phase p has
 // been read by all waves (each waits for its LDS reads before its barrier) two
 // sections later, when waves 0..3 start the read section of phase p + 1, and
 // its space is overwritten from there on.

@@ -850,7 +850,7 @@ void b2b_mlp_few_kernel(B2BParams p) {
           ring + slot * F::STAGE + j * 1024);
   };
 #pragma unroll
-  for (int st = 0; st < S; ++st) {                // n_st > S: K >= 128
+  for (int st = 0; st < S; ++st) {                // n_st >= S: K >= 128
     const Src s = next();
 #pragma unroll
     for (int j = 0; j < 8; ++j) load(s, st, j);
