@@ -307,6 +307,10 @@ def gemm_postnorm(X, W, bias=None, R=None, gamma=None, beta=None, *, w_layout=CF
     check=True reads the workspace's error word after the call (a stream
     synchronisation) and raises if a row-cluster wait gave up; pass
     check=False to keep the call asynchronous and use check_workspace later.
+    Where the workspace is optional (a query answers CF_WS_OPTIONAL_BYTES:
+    narrow rows), check=True runs on whole rows, without the synchronisation
+    and without a workspace, also if one is given; only check=False takes the
+    row clusters (128 x 256 x 256 in fp32 14.9 us against 6.8).
     """
     torch = _torch()
     M = X.shape[0]
