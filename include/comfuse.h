@@ -109,12 +109,13 @@ typedef enum {
  * and clears it.
  * Row clusters that overlap on one GPU.  Calls on several streams need
  * workspaces of their own.  A row cluster's workgroups wait for each other in
- * groups (path 0: up to 16, path 2: N / 256 .. N / 128) that share the 32 compute
- * units of an XCD, so overlapping calls are certain to complete while the sum of
- * (group size - 1) over them stays below 32: two calls always, four with groups of
- * up to 8.  More of them at once may starve each other until the bound and are
- * then reported; paths 1 and 3, and path 0 without an optional workspace, never
- * wait.
+ * groups that share the 32 compute units of an XCD.  Path 0 with N <= 1024 has
+ * groups of up to 8 with a unit each, or of up to 16 that fit a unit in pairs: four
+ * overlapping calls are certain to complete.  With N > 1024, or on path 2 (N / 256 ..
+ * N / 128 workgroups with a unit each), calls are while the sum of (group size - 1)
+ * over them stays below 32: two always.  More of them at once may starve each other
+ * until the bound and are then reported; paths 1 and 3, and path 0 without an
+ * optional workspace, never wait.
  * ------------------------------------------------------------------------ */
 typedef struct {
   size_t struct_size;            /* = sizeof(cf_postnorm_args) */

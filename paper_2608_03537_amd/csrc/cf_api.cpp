@@ -81,14 +81,18 @@ cf_status hip_status(hipError_t e, const char* what) {
 enum Path { PATH_AUTO = 0, PATH_WHOLE_ROW = 1, PATH_CLUSTER = 2, PATH_SPLIT = 3 };
 
 constexpr int kWholeRowMaxN = 768;
-// An incomplete group of peers holds its CUs while it waits, and one call has at
-// most one such group on an XCD: with at most 16 peers two overlapping calls (on
-// two streams) leave an XCD's 32 CUs room to complete one of theirs, with
-// kAutoClusterPeers four do.  (Small tiles with one peer per CU of the XCD were
-// faster for a single stream, 16 x 1024 x 1024 8.5 us against 9.1, and two such
-// calls could starve each other.)
+// An incomplete group of peers holds its places while it waits, and one call has at
+// most one such group on an XCD.  Up to N = 1024 the automatic choice leaves room to
+// complete one of kOverlap calls on as many streams (the hardware queues that HIP
+// uses by default): an XCD's 32 CUs do for groups of up to kAutoClusterPeers
+// workgroups with a CU each, twice as many places for groups of up to
+// kClusterMaxPeers small tiles that fit a CU in pairs (pick_small).  Wider rows have
+// up to 16 peers with a CU each, of which one of two calls always completes.  (Small
+// tiles with one peer per CU of the XCD were faster for a single stream, 32 x 2048 x
+// 2048 13.3 us against 16.7, and two such calls could starve each other.)
 constexpr int kClusterMaxPeers = kClusterPeers;
 constexpr int kAutoClusterPeers = 8;
+constexpr int kOverlap = 4;
 
 struct Plan {
   int kidx = -1, mode = ROWS_LOCAL, cn = 1, num_rb = 0, slots = 0, tm = 0, tn = 0;
@@ -171,6 +175,7 @@ double plan_cost(const GemmKernel& t, int64_t rounds, int64_t wgs, int64_t K, bo
   double step, start;
   if (t.epi == 3) {   // small tiles: operand stream, or fp32 MFMAs (0.42 TFLOP/s a CU)
     step = t.tm == 64 ? 0.13 + 0.07 * busy : t.tn == 64 ? 0.115 + 0.065 * busy : 0.10 + 0.09 * busy;
+    if (t.pair) step += 0.03;   // 1 and 333 x 768 x 3072 13.1 and 14.7 us, with the deep ring 11.1 and 13.7
     if (t.in_f32) step = std::max(2.0 * step, 2.0 * t.tm * t.tn * 64 / 0.42e6);
     start = cluster ? (t.tm == 64 ? 8.0 : 6.0) : t.in_f32 ? 5.0 : t.tm == 64 ? 4.0 : 3.0;
   } else if (t.tm == 64) {
@@ -211,7 +216,8 @@ double cost_128(int idx, int64_t M, int64_t N, int64_t K, int64_t batch, bool cl
 // for row clusters on the direct-to-LDS ring (loop 1, 2), the 64 x 128 tile, if
 // that is below `limit`; else -1.  cluster: column tiles must divide N into at
 // most kClusterMaxPeers peers, whose row blocks run in rounds of the groups
-// resident on an XCD (32 CUs).  Measured post-norms (us; 32 x 64 / 64 x 64 / 64 x
+// resident on an XCD (32 CUs); small tiles of more than kAutoClusterPeers peers take
+// the shorter ring.  Measured post-norms (us; 32 x 64 / 64 x 64 / 64 x
 // 128 / 128 x 128): 333 x 768 x 3072 14.1 / 17.8 / - / 26.9; 1024 x 1024 x 1024
 // 17.4 / 13.6 / 12.1 / 15.8; 2048 x 1024 x 1024 30 / 22.9 / 13.2 / 16.2; 1536 x
 // 768 x 3072 36 / 32.7 / 21.1 / 27.0; two rounds of 64 x 128 lose (3072 x 1024 x
@@ -225,9 +231,10 @@ int pick_small(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int loop,
       {32, 32, w_nk ? 1 : 2, 3}, {32, 64, w_nk ? 1 : 2, 3}, {64, 64, w_nk ? 1 : 2, 3}, {64, 128, loop, 1}};
   for (const auto& t : tiles) {
     if (t.epi == 1 && (!cluster || loop < 1)) continue;
-    const int idx = find_gemm_kernel(in_f32, t.tm, t.tn, t.loop, t.epi);
-    if (idx < 0 || (t.epi == 1 && K / 64 < gemm_kernel(idx).stages - 1)) continue;
     const int64_t rb = (M + t.tm - 1) / t.tm, cn = (N + t.tn - 1) / t.tn;
+    const int idx = find_gemm_kernel(in_f32, t.tm, t.tn, t.loop, t.epi,
+                                     t.epi == 3 && cluster && cn > kAutoClusterPeers);
+    if (idx < 0 || (t.epi == 1 && K / 64 < gemm_kernel(idx).stages - 1)) continue;
     const int64_t wgs = rb * cn * batch;
     int64_t rounds = (wgs + kAssumedCUs - 1) / kAssumedCUs;
     if (cluster) {
@@ -372,10 +379,12 @@ cf_status plan_rows(int64_t M, int64_t N, int64_t K, int in_f32, bool w_nk, int 
 
 // Row clusters: every peer group must be resident at once, so the persistent
 // grid is capped (queries the device, hence only right before a launch).
+// Groups of small tiles also leave the places of kOverlap - 1 other incomplete groups.
 cf_status cap_slots(Plan& pl) {
   if (pl.mode != ROWS_CLUSTER) return CF_OK;
-  const int slots = resident_wgs(pl.kidx) / (8 * pl.cn);
-  if (slots < 1) return fail(CF_ERR_UNSUPPORTED, "cluster path: %d peers do not fit the device", pl.cn);
+  const int places = resident_wgs(pl.kidx) / 8, slots = places / pl.cn;
+  if (slots < 1 || (gemm_kernel(pl.kidx).pair && places <= kOverlap * (pl.cn - 1)))
+    return fail(CF_ERR_UNSUPPORTED, "cluster path: %d peers do not fit the device", pl.cn);
   pl.slots = std::min(pl.slots, std::min(slots, kMaxSlots / 8));
   return CF_OK;
 }

@@ -386,9 +386,9 @@ void gemm_big_kernel(GemmRowsParams p) {
 }
 
 static const GemmKernel kTable[] = {
-    {kBigT, kBigT, 0, 1, 0, 512, 3, reinterpret_cast<const void*>(&gemm_big_kernel<false>),
+    {kBigT, kBigT, 0, 1, 0, 512, 3, 0, reinterpret_cast<const void*>(&gemm_big_kernel<false>),
      reinterpret_cast<const void*>(&gemm_big_kernel<false>)},
-    {kBigT, kBigT, 0, 2, 0, 512, 3, reinterpret_cast<const void*>(&gemm_big_kernel<true>),
+    {kBigT, kBigT, 0, 2, 0, 512, 3, 0, reinterpret_cast<const void*>(&gemm_big_kernel<true>),
      reinterpret_cast<const void*>(&gemm_big_kernel<true>)},
 };
 

@@ -11,18 +11,18 @@
 namespace cf {
 
 // Every compiled kernel, and its index by (fp32 input, tile rows, tile columns,
-// main loop, epilogue): planning a call looks up about twenty candidates, which
+// main loop, epilogue, pair): planning a call looks up about twenty candidates, which
 // a search of the table made a noticeable part of a short call's host time.
 namespace {
 struct Registry {
   std::vector<GemmKernel> all;
-  std::array<int16_t, 2 * 4 * 8 * 3 * 4> index;
-  static int key(int in_f32, int tm, int tn, int loop, int epi) {
+  std::array<int16_t, 2 * 2 * 4 * 8 * 3 * 4> index;
+  static int key(int in_f32, int tm, int tn, int loop, int epi, int pair) {
     const int r = tm == 32 ? 0 : tm == 64 ? 1 : tm == 128 ? 2 : tm == 256 ? 3 : -1;
     const int c = tn == 32 ? 0 : tn == 64 ? 1 : tn == 128 ? 2 : tn == 192 ? 3 : tn == 256 ? 4 : tn == 384 ? 5
                   : tn == 512 ? 6 : tn == 768 ? 7 : -1;
     if (r < 0 || c < 0 || loop < 0 || loop > 2 || epi < 0 || epi > 3) return -1;
-    return ((((in_f32 != 0) * 4 + r) * 8 + c) * 3 + loop) * 4 + epi;
+    return ((((pair * 2 + (in_f32 != 0)) * 4 + r) * 8 + c) * 3 + loop) * 4 + epi;
   }
   Registry() {
     index.fill(-1);
@@ -33,7 +33,7 @@ struct Registry {
       all.insert(all.end(), k, k + n);
     }
     for (size_t i = 0; i < all.size(); ++i) {
-      const int q = key(all[i].in_f32, all[i].tm, all[i].tn, all[i].loop, all[i].epi);
+      const int q = key(all[i].in_f32, all[i].tm, all[i].tn, all[i].loop, all[i].epi, all[i].pair);
       if (q >= 0 && index[q] < 0) index[q] = (int16_t)i;
     }
   }
@@ -45,8 +45,8 @@ const Registry& registry() {
 const std::vector<GemmKernel>& table() { return registry().all; }
 }  // namespace
 
-int find_gemm_kernel(int in_f32, int tm, int tn, int loop, int epi) {
-  const int q = Registry::key(in_f32, tm, tn, loop, epi);
+int find_gemm_kernel(int in_f32, int tm, int tn, int loop, int epi, int pair) {
+  const int q = Registry::key(in_f32, tm, tn, loop, epi, pair);
   return q < 0 ? -1 : registry().index[q];
 }
 

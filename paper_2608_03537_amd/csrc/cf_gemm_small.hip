@@ -12,6 +12,12 @@
 // workgroup) in flight to cover the memory latency.  The four partial tiles are
 // added through LDS in wave order.
 //
+// Pairs.  Row clusters of more than 8 peers take half the stages (48 or 64 KB), so
+// that two workgroups fit a CU and the peers of overlapping calls, which wait for
+// each other, all find a place.  The stage's next contents are on their way while
+// its MFMAs run, so little is lost: post-norm 333 x 768 x 3072 14.7 us (deep ring
+// 13.7), 333 x 768 x 768 8.8 (9.1), fp32 128 x 768 x 768 13.3 (14.5).
+//
 // Rows.  For the epilogue a row belongs to 256 / TM neighbouring lanes, so row
 // reductions are lane exchanges and every global access is a row segment.  The
 // row statistics of a tile are completed by the row-cluster exchange (the cn
@@ -31,7 +37,7 @@ namespace cf {
 
 namespace {
 
-template <typename T_, int BM_, int BN_, bool KN_>
+template <typename T_, int BM_, int BN_, bool KN_, bool PAIR_>
 struct Small {
   using T = T_;
   static constexpr int BM = BM_, BN = BN_, NW = 4, NT = 256;
@@ -41,14 +47,16 @@ struct Small {
   static constexpr int TK = 8 * EPC;               // k per 128-byte stage
   static constexpr int STAGE = (TM + TN) * 128;
   static constexpr int PX = TM / 8, PW = TN / 8;   // wave-wide loads per stage
-  static constexpr int S = BM + BN == 2 ? 4 : BM + BN == 3 ? 3 : 2;
+  static constexpr bool PAIR = PAIR_;              // two workgroups fit a CU
+  static constexpr int S = PAIR ? (BM + BN == 2 ? 2 : 1) : BM + BN == 2 ? 4 : BM + BN == 3 ? 3 : 2;
   static constexpr int RING = S * STAGE;           // one wave's ring
   static constexpr int PITCH = TN * 4 + 16;        // row of a partial tile
   static constexpr int TPR = NT / TM;              // lanes per row
   static constexpr int CPT = TN / TPR;             // columns per lane
   static constexpr int G = CPT < 8 ? CPT : 8, NG = CPT / G;   // consecutive columns, groups of them
-  static constexpr int LDS = NW * RING + 16;       // + round tag
-  static_assert(NW * TM * PITCH <= NW * RING && LDS <= 160 * 1024, "LDS budget");
+  static constexpr int TAG = NW * (RING > TM * PITCH ? RING : TM * PITCH);   // rings, partial tiles; then the round tag
+  static constexpr int LDS = TAG + 16;
+  static_assert(LDS <= (PAIR ? 80 : 160) * 1024, "LDS budget");
   static_assert(!KN || sizeof(T) == 2, "K x N: bf16");
   static_assert((PX + PW) * S < 64, "vmcnt range");
   static_assert(TM <= kRecRows, "records of kClusterPeers peers");
@@ -119,11 +127,11 @@ __device__ __forceinline__ void small_exchange(const GemmRowsParams& p, int stag
 }  // namespace
 
 template <class S>
-__global__ __launch_bounds__(256, 1) __attribute__((amdgpu_waves_per_eu(1, 1)))
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(S::PAIR ? 2 : 1, S::PAIR ? 2 : 1)))
 void gemm_small_kernel(GemmRowsParams p) {
   using T = typename S::T;
   __shared__ __attribute__((aligned(16))) char smem[S::LDS];
-  unsigned* const tag_lds = reinterpret_cast<unsigned*>(smem + S::NW * S::RING);
+  unsigned* const tag_lds = reinterpret_cast<unsigned*>(smem + S::TAG);
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 31, lg = lane >> 5;
@@ -497,16 +505,21 @@ void gemm_small_kernel(GemmRowsParams p) {
 template <class S>
 static GemmKernel small_entry() {
   const void* f = reinterpret_cast<const void*>(&gemm_small_kernel<S>);
-  return GemmKernel{S::TM, S::TN, std::is_same<typename S::T, float>::value ? 1 : 0, S::KN ? 2 : 1, 3, S::NT, 1, f, f};
+  return GemmKernel{S::TM, S::TN, std::is_same<typename S::T, float>::value ? 1 : 0, S::KN ? 2 : 1, 3, S::NT, 1, S::PAIR ? 1 : 0, f, f};
 }
 
 const GemmKernel* gemm_kernels_small(int* n) {
   static const GemmKernel table[] = {
-      small_entry<Small<bf16_t, 1, 1, false>>(), small_entry<Small<bf16_t, 1, 2, false>>(),
-      small_entry<Small<bf16_t, 2, 2, false>>(), small_entry<Small<bf16_t, 1, 1, true>>(),
-      small_entry<Small<bf16_t, 1, 2, true>>(),  small_entry<Small<bf16_t, 2, 2, true>>(),
-      small_entry<Small<float, 1, 1, false>>(),  small_entry<Small<float, 1, 2, false>>(),
-      small_entry<Small<float, 2, 2, false>>(),
+      small_entry<Small<bf16_t, 1, 1, false, false>>(), small_entry<Small<bf16_t, 1, 2, false, false>>(),
+      small_entry<Small<bf16_t, 2, 2, false, false>>(), small_entry<Small<bf16_t, 1, 1, true, false>>(),
+      small_entry<Small<bf16_t, 1, 2, true, false>>(),  small_entry<Small<bf16_t, 2, 2, true, false>>(),
+      small_entry<Small<float, 1, 1, false, false>>(),  small_entry<Small<float, 1, 2, false, false>>(),
+      small_entry<Small<float, 2, 2, false, false>>(),
+      small_entry<Small<bf16_t, 1, 1, false, true>>(),  small_entry<Small<bf16_t, 1, 2, false, true>>(),
+      small_entry<Small<bf16_t, 2, 2, false, true>>(),  small_entry<Small<bf16_t, 1, 1, true, true>>(),
+      small_entry<Small<bf16_t, 1, 2, true, true>>(),   small_entry<Small<bf16_t, 2, 2, true, true>>(),
+      small_entry<Small<float, 1, 1, false, true>>(),   small_entry<Small<float, 1, 2, false, true>>(),
+      small_entry<Small<float, 2, 2, false, true>>(),
   };
   *n = (int)(sizeof(table) / sizeof(table[0]));
   return table;

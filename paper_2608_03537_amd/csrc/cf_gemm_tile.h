@@ -1560,7 +1560,7 @@ inline const void* gemm_persist_fn() {
 // Registry entry of one instantiation: <tile shape S, main loop, epilogue>.
 #define CF_GEMM_ENTRY(S, LOOP, EPI)                                                                  \
   GemmKernel {                                                                                       \
-    S::TM, S::TN, std::is_same<typename S::T, float>::value ? 1 : 0, LOOP, EPI, S::NT, S::STAGES,    \
+    S::TM, S::TN, std::is_same<typename S::T, float>::value ? 1 : 0, LOOP, EPI, S::NT, S::STAGES, 0, \
         reinterpret_cast<const void*>(&gemm_rows_kernel<S, LOOP, EPI, false>),                       \
         gemm_persist_fn<S, LOOP, EPI>()                                                              \
   }

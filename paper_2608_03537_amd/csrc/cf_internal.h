@@ -116,6 +116,7 @@ struct RowKernelParams {
 struct GemmKernel {
   int tm, tn, in_f32, loop, epi, threads;
   int stages;   // direct-to-LDS ring depth (needs K / k_per_stage >= stages - 1); 0 for other loops
+  int pair;     // small tiles with a shorter ring: two workgroups fit a CU (row clusters of more than 8 peers)
   const void* fn;           // one tile per workgroup
   const void* fn_persist;   // workgroups loop over row-block slots (row-cluster path with a capped grid)
 };
@@ -126,7 +127,7 @@ const GemmKernel* gemm_kernels_split(int* n);  // split-N GEMM pass (both main l
 const GemmKernel* gemm_kernels_kn(int* n);     // direct-to-LDS pipeline, bf16 W stored K x N
 const GemmKernel* gemm_kernels_big(int* n);    // 256 x 256 tiles, plain epilogue
 const GemmKernel* gemm_kernels_small(int* n);  // 32 / 64-row tiles, split K in the workgroup, any epilogue (epi 3)
-int find_gemm_kernel(int in_f32, int tm, int tn, int loop, int epi);   // -1 if none
+int find_gemm_kernel(int in_f32, int tm, int tn, int loop, int epi, int pair = 0);   // -1 if none
 const GemmKernel& gemm_kernel(int idx);
 int resident_wgs(int idx);   // co-resident workgroups of this kernel on the device
 

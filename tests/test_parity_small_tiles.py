@@ -57,6 +57,9 @@ def _chain(inp, layout, dtype, kind):
     (1000, 528, 768),   # 64 x 128 tiles (bf16 on the ring) or 64 x 64, ragged last row block
     (999, 1040, 1024),  # K past whole stages keeps the 64 x 64 tiles
     (2047, 256, 1024),  # 64 x 128 tiles, one row short of a row block
+    (700, 1040, 512),   # 32 x 64 tiles of 8 peers: the deep ring
+    (1500, 1040, 512),  # 64 x 64 tiles of 8 peers, the deep ring, ragged last row block
+    (600, 784, 768),    # 64 x 64 tiles of 12 peers: the short ring, a quarter stage past whole stages
 ])
 def test_row_clusters(M, K, N, layout, dtype, kind):
     inp = I.postnorm_inputs(M, K, N, dtype, seed=51, bias_std=0.5, gamma="uniform", beta_std=0.3)
@@ -133,7 +136,8 @@ def test_peer_wait_failure_is_reported():
 
 
 @pytest.mark.parametrize("dtype,M,K,N", [("f32", 128, 256, 256), ("bf16", 200, 400, 224), ("f32", 70, 272, 320),
-                                         ("bf16", 9000, 768, 768)])
+                                         ("bf16", 9000, 768, 768),
+                                         ("bf16", 33, 272, 352), ("f32", 33, 272, 352)])   # 32 x 32 tiles, 11 peers
 def test_optional_workspace(dtype, M, K, N):
     """Shapes whose workspace is optional: whole rows without one (or with one too small), row clusters with it; the
     helper leaves it out unless check=False."""
@@ -165,8 +169,8 @@ def test_optional_workspace(dtype, M, K, N):
     ("bf16", 16, 1024, 1024, 32), ("bf16", 64, 2048, 2048, 64), ("bf16", 33, 1040, 1024, 32), ("f32", 32, 640, 640, 32),
     ("f32", 100, 512, 768, 32), ("bf16", 5, 272, 1280, 128)])
 def test_groups_leave_room_for_another_call(dtype, M, K, N, rows):
-    """An XCD has 32 CUs, and a waiting group holds one per peer: with at most 16 peers two overlapping calls always
-    complete.  The peers are counted by the records that a call on a fresh workspace leaves, `rows` from each."""
+    """An XCD has 32 CUs, and a waiting group holds one or, in pairs, half of one per peer: with at most 16 peers two
+    (in pairs four) overlapping calls always complete.  The peers are counted by the records that a call on a fresh workspace leaves, `rows` from each."""
     inp = I.postnorm_inputs(M, K, N, dtype, seed=56, with_affine=False)
     ws = torch.zeros(64 << 20, dtype=torch.uint8, device="cuda")
     cf.gemm_postnorm(dev(inp.X, dtype), dev(I.lay_out_weight(inp.W, "nk"), dtype), dev(inp.bias, "f32"),
@@ -179,13 +183,28 @@ def test_groups_leave_room_for_another_call(dtype, M, K, N, rows):
     assert 1 < peers <= 16 and peers == int(peers), peers
 
 
-def test_two_streams_of_row_clusters():
-    """Calls with the largest groups on two streams at once, each with a workspace of its own, all on one XCD: all of
-    them complete and are right."""
+@pytest.mark.parametrize("M,K,N,groups", [(1200, 512, 768, 38), (2000, 512, 1024, 32)])
+def test_pairs_on_a_cu(M, K, N, groups):
+    """Row clusters of 12 and 16 peers whose workgroups fit a CU in pairs: the call runs all its row blocks' groups at
+    once, where a CU per workgroup would leave room for 16.  Every group has left its round counter."""
+    dtype = "f32"
+    inp = I.postnorm_inputs(M, K, N, dtype, seed=58, with_affine=False)
+    ws = torch.zeros(cf.CF_WS_HEADER_BYTES, dtype=torch.uint8, device="cuda")
+    Y = cf.gemm_postnorm(dev(inp.X, dtype), dev(I.lay_out_weight(inp.W, "nk"), dtype), dev(inp.bias, "f32"),
+                         dev(inp.R, dtype), eps=inp.eps, ws=ws)
+    ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, None, None, 1.0, inp.eps)
+    assert_close_f32(host(Y), ref, "pairs")
+    assert int(ws[256:256 + 64 * 8].view(torch.int64).count_nonzero()) == groups
+
+
+@pytest.mark.parametrize("count", [2, 4])
+def test_streams_of_row_clusters(count):
+    """Calls with the largest groups on `count` streams at once, each with a workspace of its own, all on one XCD: all
+    of them complete and are right."""
     inp = I.postnorm_inputs(16, 512, 1024, "bf16", seed=57, with_affine=False)
     X, W, b, R = dev(inp.X), dev(I.lay_out_weight(inp.W, "nk")), dev(inp.bias, "f32"), dev(inp.R)
     ref = O.postnorm(inp.X, inp.W, inp.bias, inp.R, None, None, 1.0, inp.eps)
-    streams = [torch.cuda.Stream() for _ in range(2)]
+    streams = [torch.cuda.Stream() for _ in range(count)]
     outs = [[torch.empty_like(R) for _ in range(50)] for _ in streams]
     torch.cuda.synchronize()
     for i in range(50):
