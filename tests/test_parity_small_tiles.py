@@ -54,7 +54,7 @@ def _chain(inp, layout, dtype, kind):
     (33, 1040, 1024),   # one row past a tile, K a quarter stage past whole stages, 16 peers
     (65, 48, 768),      # less than one stage: three waves have no k
     (300, 272, 640),    # 32 x 64 tiles, an odd number of stages per wave
-    (1000, 528, 768),   # 64 x 128 tiles (bf16 on the ring) or 64 x 64, ragged last row block
+    (1000, 528, 768),   # 64 x 64 tiles (K past whole stages), ragged last row block
     (999, 1040, 1024),  # K past whole stages keeps the 64 x 64 tiles
     (2047, 256, 1024),  # 64 x 128 tiles, one row short of a row block
     (700, 1040, 512),   # 32 x 64 tiles of 8 peers: the deep ring
